@@ -298,6 +298,13 @@ __device__ inline uint32_t wave_incl_scan_u32(uint32_t x) {
   return x;
 }
 
+// A workgroup barrier that orders LDS accesses only: it waits for this wave's
+// LDS operations, not for its global loads and stores in flight (which
+// __syncthreads also waits for).
+__device__ inline void lds_barrier() {
+  __asm__ __volatile__("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // ----------------------------------------------------------------- atomics
 
 template <typename T>

@@ -56,13 +56,6 @@ __device__ inline TabLds carve_tab(unsigned char* sp, int64_t M) {
   return t;
 }
 
-// A workgroup barrier that orders LDS accesses only: it waits for this wave's
-// LDS operations, not for its global loads and stores in flight (which
-// __syncthreads also waits for).
-__device__ inline void lds_barrier() {
-  __asm__ __volatile__("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 __device__ void instance_table(const ProblemDev& p, ITab it, unsigned char* smem) {
   const int M = int(p.M);
   const int tid = threadIdx.x;

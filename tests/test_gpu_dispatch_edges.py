@@ -1,0 +1,46 @@
+"""GPU parity at the edges of the dispatch rules: sizes and values at which a
+pass moves from one kernel or number format to another, each against the CPU
+oracle, bit-exact."""
+import numpy as np
+import pytest
+
+from paper_2601_05109_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover - collected on CPU hosts too
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2601_05109_amd import nalar  # noqa: E402
+from test_gpu_parity import _one_type, check, policy  # noqa: E402,F401
+
+
+# ---------------------------------------------------------------- greedy routing
+
+@pytest.mark.parametrize("n_inst", [1, 2, 8, 9, 16, 17, 64])
+@pytest.mark.parametrize("spread", ["near", "limit", "far", "huge-estimates", "huge-penalty"])
+def test_greedy_relative_costs(policy, n_inst, spread):  # noqa: F811
+    """The greedy chain's 32-bit relative costs: loads close together; loads at
+    the distance where a relative load stops fitting (2^29 us with 8 candidates,
+    2^28 with 16, 2^26 with 64); loads up to 2^60 apart; service times and a
+    migration penalty that never fit.  5,000 futures wrap the queue and leave a
+    partial batch."""
+    rng = np.random.default_rng(n_inst * 31 + len(spread))
+    n = 5000
+    loads = rng.integers(0, 10**6, n_inst)
+    est = rng.integers(0, 10**6, n)
+    mig = 200_000
+    if spread == "limit":
+        loads = loads + rng.choice([0, 1 << 26, (1 << 26) - 1, 1 << 28, 1 << 29, (1 << 29) - 1], n_inst)
+    elif spread == "far":
+        loads = loads + rng.choice([0, 1 << 31, 1 << 40, (1 << 60) - 10**6], n_inst)
+    elif spread == "huge-estimates":
+        est[rng.random(n) < 0.01] = 1 << 36
+    elif spread == "huge-penalty":
+        mig = 1 << 60
+    loc = np.where(rng.random(n) < 0.4, rng.integers(0, n_inst, n), -1)
+    p = _one_type(n_inst, np.minimum(loads, 1 << 60), rng.integers(300, 3000, n_inst), est, loc=loc, mig=mig)
+    G = nalar.NALAR_ROUTE_GREEDY
+    check(policy, p, f"greedy {n_inst} {spread}", policy=G)
+    check(policy, p, f"greedy {n_inst} {spread} stateful", policy=G | nalar.NALAR_ROUTE_STATEFUL)
