@@ -21,8 +21,7 @@
 //   [weighted] -> NALAR_ROUTE_WEIGHTED only: the weighted instances are
 //               tabulated before the sweep (their weights validated), and the
 //               weighted types' futures are dealt out after the sort
-// with one stream synchronisation after the sort (and one after greedy or
-// weighted routing).  The bucketed sort is used once a previous pass has given a key
+// with one stream synchronisation at the end.  The bucketed sort is used once a previous pass has given a key
 // range and at most kBucketMaxReady futures were ready; if a bucket
 // overflows, the kernel reports "tiled", and after the synchronisation the
 // host resets the control block, sweeps again without buckets and runs the
@@ -405,6 +404,13 @@ ProblemDev device_view(const nalar_problem* p, uint32_t policy) {
                     p->inst_speed_permille, p->wf_priority, p->inst_weight};
 }
 
+GreedyArgs greedy_args(nalar_policy* h, const nalar_problem* p, const nalar_result* r, uint32_t policy,
+                       const Ctrl* ctrl, int32_t passes_launched) {
+  return GreedyArgs{r->order, ctrl, passes_launched, p->type, p->est_us, p->loc, p->inst_type, p->inst_load_us,
+                    p->inst_speed_permille, int32_t(p->n_instances), (policy & NALAR_ROUTE_STATEFUL) ? 1 : 0,
+                    p->migration_cost_us, r->route, r->cost_us, h->host};
+}
+
 struct Timer {
   nalar_policy* h;
   int n = 0;
@@ -674,6 +680,8 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
     wa.M = int32_t(M);
     wa.stateful = (policy & NALAR_ROUTE_STATEFUL) ? 1 : 0;
     wa.mig = p->migration_cost_us;
+    wa.order = r->order;
+    wa.N = N;
     wa.route = r->route;
     wa.cost = r->cost_us;
     wa.ctrl = ctrl;
@@ -786,6 +794,25 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
   __atomic_store_n(&h->host->max_bucket, 0u, __ATOMIC_RELAXED);       // written by the large-bucket sort
   __atomic_store_n(&h->host->split_nb, 0u, __ATOMIC_RELAXED);         // written with new splitters
   __atomic_store_n(&h->host->status, 0xFFFFFFFFu, __ATOMIC_RELEASE);  // the kernels overwrite it
+  __atomic_store_n(&h->host->aux_status, 0u, __ATOMIC_RELEASE);       // written by the greedy routing
+  // Load-aware or weighted routing over the finished order, behind a sort
+  // without the host in between (about 20 us of completion and launch per
+  // pass when the host waited for the ready count first); the kernels do
+  // nothing when the sort has not finished the order, and are launched again
+  // behind the next one.
+  auto launch_ordered_routing = [&]() -> int {
+    if (N <= 0 || M <= 0) return NALAR_OK;
+    if (policy & NALAR_ROUTE_GREEDY) {
+      const GreedyArgs g = greedy_args(h, p, r, policy, ctrl, sa.passes_launched);
+      NALAR_LAUNCH("route_greedy", launch_route_greedy(s, g));
+    } else if (policy & NALAR_ROUTE_WEIGHTED) {
+      wa.passes_launched = sa.passes_launched;
+      const hipError_t we = launch_route_weighted(s, wa, Timer::cb, &tm);
+      if (we != hipSuccess) return hip_fail(h, we, "weighted");
+    }
+    return NALAR_OK;
+  };
+  int rrc;
   bool tiled = bk.nb == 0;
   if (!tiled) {
     if (bk.bins) {
@@ -794,6 +821,7 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
       NALAR_LAUNCH("sort_bucket", launch_bucket_sort(s, sa, bk));
       if (want_split) NALAR_LAUNCH("splitters", launch_splitters(s, sa));
     }
+    if ((rrc = launch_ordered_routing()) != NALAR_OK) return rrc;
     tm.end();
     e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
@@ -852,6 +880,7 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
     e = launch_slack_sort(s, sa, 0, kSortLaunched - 1, Timer::cb, &tm);
     if (e != hipSuccess) return hip_fail(h, e, "sort");
     if (want_split) NALAR_LAUNCH("splitters", launch_splitters(s, sa));
+    if ((rrc = launch_ordered_routing()) != NALAR_OK) return rrc;
     tm.end();
     e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
@@ -861,6 +890,7 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
       e = launch_slack_sort(s, sa, kSortLaunched, kMaxSortPasses - 1, Timer::cb, &tm);
       if (e != hipSuccess) return hip_fail(h, e, "sort");
       if (want_split) NALAR_LAUNCH("splitters", launch_splitters(s, sa));
+      if ((rrc = launch_ordered_routing()) != NALAR_OK) return rrc;
       tm.end();
       e = hipStreamSynchronize(s);
       if (e != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
@@ -879,29 +909,8 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
     h->split_nb = int(snb);
     if (snb > 0) h->split_cur ^= 1;
   }
-  if ((policy & NALAR_ROUTE_GREEDY) && r->n_ready > 0 && M > 0) {
-    // route again in output order with running loads (one wavefront per type)
-    __atomic_store_n(&h->host->aux_status, 0u, __ATOMIC_RELEASE);
-    GreedyArgs g{r->order, r->n_ready, p->type, p->est_us, p->loc, p->inst_type, p->inst_load_us,
-                 p->inst_speed_permille, int32_t(M), (policy & NALAR_ROUTE_STATEFUL) ? 1 : 0,
-                 p->migration_cost_us, r->route, r->cost_us, h->host};
-    NALAR_LAUNCH("route_greedy", launch_route_greedy(s, g));
-    tm.end();
-    e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
-    if (__atomic_load_n(&h->host->aux_status, __ATOMIC_ACQUIRE) & kStRange)
-      return fail(h, NALAR_ERANGE, "an instance load exceeds 2^62 us under load-aware routing");
-  }
-  if ((policy & NALAR_ROUTE_WEIGHTED) && r->n_ready > 0 && M > 0) {
-    wa.order = r->order;
-    wa.R = r->n_ready;
-    wa.tiles = weighted_tiles(r->n_ready);
-    e = launch_route_weighted(s, wa, Timer::cb, &tm);
-    if (e != hipSuccess) return hip_fail(h, e, "weighted");
-    tm.end();
-    e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
-  }
+  if ((policy & NALAR_ROUTE_GREEDY) && (__atomic_load_n(&h->host->aux_status, __ATOMIC_ACQUIRE) & kStRange))
+    return fail(h, NALAR_ERANGE, "an instance load exceeds 2^62 us under load-aware routing");
 #undef NALAR_LAUNCH
   if (h->timing) {
     h->n_timed = tm.n;
@@ -1049,6 +1058,11 @@ int nalar::policy_pass_incremental(nalar_policy* h, const nalar_problem* p, nala
   __atomic_store_n(&h->host->split_nb, 0u, __ATOMIC_RELAXED);
   __atomic_store_n(&h->host->status, 0xFFFFFFFFu, __ATOMIC_RELEASE);
   NALAR_LAUNCH("sort_bin", launch_bin_sort(s, sa, bk));
+  if ((policy & NALAR_ROUTE_GREEDY) && M > 0) {
+    __atomic_store_n(&h->host->aux_status, 0u, __ATOMIC_RELEASE);
+    const GreedyArgs g = greedy_args(h, p, r, policy, ctrl, sa.passes_launched);
+    NALAR_LAUNCH("route_greedy", launch_route_greedy(s, g));
+  }
   if (r->rem_us) NALAR_LAUNCH("rem_copy", hipMemcpyAsync(r->rem_us, st.rem, sizeof(int64_t) * size_t(N),
                                                          hipMemcpyDeviceToDevice, s));
   tm.end();
@@ -1071,18 +1085,8 @@ int nalar::policy_pass_incremental(nalar_policy* h, const nalar_problem* p, nala
   const uint32_t snb = __atomic_load_n(&h->host->split_nb, __ATOMIC_ACQUIRE);
   h->split_nb = int(snb);
   if (snb > 0) h->split_cur ^= 1;
-  if ((policy & NALAR_ROUTE_GREEDY) && r->n_ready > 0 && M > 0) {
-    __atomic_store_n(&h->host->aux_status, 0u, __ATOMIC_RELEASE);
-    GreedyArgs g{r->order, r->n_ready, p->type, p->est_us, p->loc, p->inst_type, p->inst_load_us,
-                 p->inst_speed_permille, int32_t(M), (policy & NALAR_ROUTE_STATEFUL) ? 1 : 0,
-                 p->migration_cost_us, r->route, r->cost_us, h->host};
-    NALAR_LAUNCH("route_greedy", launch_route_greedy(s, g));
-    tm.end();
-    e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
-    if (__atomic_load_n(&h->host->aux_status, __ATOMIC_ACQUIRE) & kStRange)
-      return fail(h, NALAR_ERANGE, "an instance load exceeds 2^62 us under load-aware routing");
-  }
+  if ((policy & NALAR_ROUTE_GREEDY) && (__atomic_load_n(&h->host->aux_status, __ATOMIC_ACQUIRE) & kStRange))
+    return fail(h, NALAR_ERANGE, "an instance load exceeds 2^62 us under load-aware routing");
 #undef NALAR_LAUNCH
   if (h->timing) {
     h->n_timed = tm.n;

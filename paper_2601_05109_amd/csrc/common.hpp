@@ -140,6 +140,14 @@ __host__ __device__ inline int32_t slot_pack(int32_t route, int lvl) {
 __host__ __device__ inline int32_t slot_route(int32_t packed) { return int32_t(int16_t(packed & 0xFFFF)); }
 __host__ __device__ inline int slot_level(int32_t packed) { return int((uint32_t(packed) >> 16) & 0xFFu); }
 
+// Whether the sort that wrote the pass's output has finished it: no error, no
+// overflow (the host sorts again) and no digit passes still to run.  Kernels
+// that follow the sort in the stream without the host in between ask this
+// first; the host launches them again behind a later sort.
+__device__ inline bool sort_finished(const Ctrl* c, int passes_launched) {
+  return (c->status | c->status_sweep | c->bucket_overflow) == 0 && int(c->sort_npass) <= passes_launched;
+}
+
 // Written by the last kernel of a pass into pinned host memory.
 struct HostStatus {
   uint32_t status;

@@ -147,10 +147,12 @@ struct BlockSweepArgs {
   int64_t plog_cap;
 };
 
-// Load-aware routing over the ordered ready futures (greedy.hip).
+// Load-aware routing over the ordered ready futures (greedy.hip), launched
+// behind the sort; does nothing unless the sort has finished the order.
 struct GreedyArgs {
   const int32_t* order;         // [R] the pass's output order
-  int64_t R;
+  const Ctrl* ctrl;             // the pass's control block: R and whether the order is final
+  int32_t passes_launched;      // as in SortArgs
   const int32_t* type;
   const int64_t* est;
   const int32_t* loc;
@@ -169,10 +171,12 @@ hipError_t launch_route_greedy(hipStream_t s, const GreedyArgs& g);
 // Weighted routing over the ordered ready futures (weighted.hip).  The table
 // kernel also checks every weight against NALAR_WEIGHT_MAX (kStInval into
 // ctrl->status, so it runs before the sweep and the error keeps its
-// precedence); the other kernels run after a successful pass.
+// precedence); the other kernels are launched behind the sort and do nothing
+// unless it has finished the order.
 struct WeightedArgs {
   const int32_t* order;         // [R] the pass's output order
-  int64_t R;
+  int64_t N;                    // futures: R <= N bounds the grids
+  int32_t passes_launched;      // as in SortArgs
   const int32_t* type;
   const int64_t* est;
   const int32_t* loc;
@@ -185,7 +189,7 @@ struct WeightedArgs {
   int64_t mig;
   int32_t* route;               // [R] overwritten for weighted futures
   int64_t* cost;                // [R] or NULL
-  Ctrl* ctrl;                   // validation status of the pass
+  Ctrl* ctrl;                   // validation status of the pass, then R
   // scratch: the weighted instances sorted by (type, index)
   int32_t* wt_type;
   int32_t* wt_idx;
@@ -194,10 +198,9 @@ struct WeightedArgs {
   int32_t* wt_first;
   int32_t* wt_cnt;
   int32_t* n_wt;
-  uint32_t* counts;             // [tiles][NALAR_MAX_INSTANCES]
-  int64_t tiles;                // weighted_tiles(R)
+  uint32_t* counts;             // [weighted_tiles(N)][NALAR_MAX_INSTANCES]
 };
-int64_t weighted_tiles(int64_t R);
+int64_t weighted_tiles(int64_t N);
 hipError_t launch_weighted_table(hipStream_t s, const WeightedArgs& g);
 hipError_t launch_route_weighted(hipStream_t s, const WeightedArgs& g, void (*mark)(void*, const char*),
                                  void* ctx);

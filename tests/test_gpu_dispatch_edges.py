@@ -44,3 +44,34 @@ def test_greedy_relative_costs(policy, n_inst, spread):  # noqa: F811
     G = nalar.NALAR_ROUTE_GREEDY
     check(policy, p, f"greedy {n_inst} {spread}", policy=G)
     check(policy, p, f"greedy {n_inst} {spread} stateful", policy=G | nalar.NALAR_ROUTE_STATEFUL)
+
+
+# ---------------------------------------------------------------- weighted routing
+
+def _independent(n, m, n_types, seed, done_share=0.0):
+    """n one-future workflows of n_types types over m instances (some types
+    without one), with state on an instance for half the futures."""
+    rng = np.random.default_rng(seed)
+    now = 10_000
+    return wl.Problem(f"independent-{n}", now, 150_000, np.arange(n, dtype=np.int32),
+                      rng.integers(0, n_types, n).astype(np.int32), rng.integers(0, 10**6, n).astype(np.int64),
+                      (rng.random(n) < done_share).astype(np.uint8),
+                      np.where(rng.random(n) < 0.5, rng.integers(0, m, n), -1).astype(np.int32),
+                      np.zeros(n + 1, np.int32), np.zeros(0, np.int32),
+                      (now + rng.integers(0, 10**7, n)).astype(np.int64),
+                      rng.integers(0, n_types, m).astype(np.int32), rng.integers(0, 10**6, m).astype(np.int64),
+                      rng.integers(300, 3000, m).astype(np.int32), wf_contiguous=True)
+
+
+@pytest.mark.parametrize("n,m,n_types", [(1, 1, 1), (64, 5, 2), (1023, 40, 63), (1024, 40, 64), (1025, 40, 65),
+                                         (4097, 1024, 130), (262_144, 64, 8), (262_145, 64, 8), (300_001, 200, 70)])
+def test_weighted_tiles(policy, n, m, n_types):  # noqa: F811
+    """Weighted routing around its tile of 1,024 positions, the types with and
+    without a direct slot (64), and 256 tiles, where the scan launch begins."""
+    p = _independent(n, m, n_types, n + m)
+    W = nalar.NALAR_ROUTE_WEIGHTED
+    w = np.random.default_rng(n).integers(0, 4, m).astype(np.uint32)
+    for rep in range(2):  # a first pass (tiled sort) and a planned one
+        check(policy, p, f"weighted n={n} pass {rep}", policy=W, weights=w)
+    check(policy, p, f"weighted stateful n={n}", policy=W | nalar.NALAR_ROUTE_STATEFUL | nalar.NALAR_ORDER_LPT,
+          weights=w)
