@@ -960,7 +960,7 @@ int nalar::policy_reserve(nalar_policy* h, int64_t N, int64_t E, int64_t W) {
 // pass's splitters and sorted with ties by (wf, id).  Everything the store
 // keeps is its own; the rest is this handle's arena, as in a full pass.
 int nalar::policy_pass_incremental(nalar_policy* h, const nalar_problem* p, nalar_result* r,
-                                   const IncStore& st) {
+                                   IncStore& st) {
   h->err.clear();
   h->timed_valid = false;
   int rc = check_problem(h, p, r);
@@ -1007,21 +1007,26 @@ int nalar::policy_pass_incremental(nalar_policy* h, const nalar_problem* p, nala
     NALAR_LAUNCH("reset", launch_reset(s, need_reset ? ctrl : nullptr, bk.cnt, need_clear ? bk.nb : 0));
   as.bcnt_clean[cur] = false;
   // the appended futures (and the one before them, for the contiguity rule)
+  const IncPack pack{st.fl, st.n_prev, st.ic};
   NALAR_LAUNCH("nodes", launch_nodes(s, pd, ctrl, A.ctrl[nxt], A.itab, A.wf_off, contiguous ? 1 : 0,
-                                     st.n_prev > 0 ? st.n_prev - 1 : 0));
+                                     st.n_prev > 0 ? st.n_prev - 1 : 0, nullptr, &pack));
   IncArgs ia{};
   ia.p = pd;
   ia.n_prev = st.n_prev;
   ia.log = st.log;
   ia.n_log = st.n_log;
   ia.rem = st.rem;
-  ia.inA = st.inA;
-  ia.dnb = st.dnb;
+  ia.rem_out = r->rem_us;
+  ia.fl = st.fl;
   ia.mxA = st.mxA;
   ia.cntA = st.cntA;
   ia.light = st.light;
   ia.heavy = st.heavy;
-  ia.rlist = st.rlist;
+  ia.rbits = st.rbits;
+  ia.hv = st.hv;
+  ia.hv_n = st.hv_n;
+  ia.hv_cap = st.hv_cap;
+  ia.rheavy = st.rheavy;
   ia.ic = st.ic;
   ia.ctrl = ctrl;
   ia.itab = A.itab;
@@ -1029,13 +1034,16 @@ int nalar::policy_pass_incremental(nalar_policy* h, const nalar_problem* p, nala
   ia.bk_clear = A.bcnt[nxt];
   ia.bk_clear_n = A.capB > 0 ? A.capB : 0;
   ia.stg_oslack = A.stg_oslack;
-  NALAR_LAUNCH("inc_pack", launch_inc_pack(s, ia));
-  NALAR_LAUNCH("inc_clear", launch_inc_clear(s, reinterpret_cast<uint32_t*>(st.ic), sizeof(IncCtrl) / 4));
-  e = launch_inc_closure(s, ia, h->cus, Timer::cb, &tm);
+  ia.host = h->host;
+  // rounds with a launch of their own: as deep as the last pass had work (work
+  // that comes deeper is done by the tail's one workgroup, and raises the next
+  // plan); an empty round costs a launch, 4 us
+  e = launch_inc_closure(s, ia, h->cus, 1 + int(st.rounds & 0xFFu), Timer::cb, &tm);
   if (e != hipSuccess) return hip_fail(h, e, "inc_closure");
   NALAR_LAUNCH("inc_scan", launch_inc_scan(s, ia, h->cus));
-  e = launch_inc_sweep(s, ia, h->cus, Timer::cb, &tm);
+  e = launch_inc_sweep(s, ia, h->cus, 1 + int(st.rounds >> 8), Timer::cb, &tm);
   if (e != hipSuccess) return hip_fail(h, e, "inc_sweep");
+  __atomic_store_n(&h->host->inc_rounds, kIncRoundsAll, __ATOMIC_RELEASE);
   NALAR_LAUNCH("inc_ready", launch_inc_ready(s, ia, h->cus));
   as.bcnt_clean[nxt] = true;
 
@@ -1048,6 +1056,7 @@ int nalar::policy_pass_incremental(nalar_policy* h, const nalar_problem* p, nala
   sa.split_next = A.split[h->split_cur ^ 1];
   sa.split_min = 1;
   sa.tie_wf = p->wf;
+  sa.tie_packed = W <= kPackWf ? 1 : 0;
   sa.p = pd;
   sa.passes_launched = kMaxSortPasses;
   sa.order = r->order;
@@ -1063,13 +1072,12 @@ int nalar::policy_pass_incremental(nalar_policy* h, const nalar_problem* p, nala
     const GreedyArgs g = greedy_args(h, p, r, policy, ctrl, sa.passes_launched);
     NALAR_LAUNCH("route_greedy", launch_route_greedy(s, g));
   }
-  if (r->rem_us) NALAR_LAUNCH("rem_copy", hipMemcpyAsync(r->rem_us, st.rem, sizeof(int64_t) * size_t(N),
-                                                         hipMemcpyDeviceToDevice, s));
   tm.end();
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
   const uint32_t sts = __atomic_load_n(&h->host->status, __ATOMIC_ACQUIRE);
   if (sts == 0xFFFFFFFFu) return fail(h, NALAR_EDEVICE, "status was not written");
+  st.rounds = __atomic_load_n(&h->host->inc_rounds, __ATOMIC_ACQUIRE);
   if (sts == kStatusTiled) {
     h->bin_max = 0;
     return kIncFallbackOverflow;

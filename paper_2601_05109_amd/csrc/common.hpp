@@ -148,6 +148,15 @@ __device__ inline bool sort_finished(const Ctrl* c, int passes_launched) {
   return (c->status | c->status_sweep | c->bucket_overflow) == 0 && int(c->sort_npass) <= passes_launched;
 }
 
+// The incremental pass has no levels; up to kPackWf workflows, its records
+// carry the workflow there instead, so that the sort's ties (key, wf, id) need no
+// gather by id.
+constexpr int64_t kPackWf = 65536;
+__host__ __device__ inline int32_t slot_pack_wf(int32_t route, int32_t wf) {
+  return int32_t((uint32_t(route) & 0xFFFFu) | (uint32_t(wf) << 16));
+}
+__host__ __device__ inline int32_t slot_wf(int32_t packed) { return int32_t(uint32_t(packed) >> 16); }
+
 // Written by the last kernel of a pass into pinned host memory.
 struct HostStatus {
   uint32_t status;
@@ -159,6 +168,7 @@ struct HostStatus {
   uint32_t level_mask; // priority levels of this pass (bit l: level l; with levels only)
   uint32_t max_bucket; // futures in the fullest bucket (large-bucket sort only, else 0)
   uint32_t split_nb;   // bins the splitters written by this pass are for (0: none)
+  uint32_t inc_rounds; // deepest rounds of an incremental pass that had work: closure | sweep << 8
 };
 
 // Resets a control block for a later pass (run by one workgroup).

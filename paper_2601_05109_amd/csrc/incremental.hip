@@ -39,18 +39,22 @@ namespace nalar {
 namespace {
 
 constexpr int kIncThreads = 256;
-constexpr int kIncTail = 3;       // rounds from here on run in one workgroup (k_inc_*_tail)
-constexpr int kIncHeavy = 64;     // more dependencies: one workgroup expands the future
+constexpr int kIncTail = 3;       // rounds from here on always run in one workgroup (k_inc_*_tail)
+constexpr int kIncTailThreads = 1024;
 constexpr int kScanPer = 8;       // futures per thread in the scan (kIncThreads apart)
-constexpr int kReadyPer = 4;      // ready futures per thread and chunk in the ready kernel
 
-__device__ inline bool bit_set_new(uint32_t* bits, int32_t v) {
+// A future's flags: closure membership and done, one bit of each word of a pair.
+__device__ inline bool bit_set_new(uint2* fl, int32_t v) {
   const uint32_t m = 1u << (uint32_t(v) & 31u);
-  return (atomicOr(&bits[uint32_t(v) >> 5], m) & m) == 0u;
+  return (atomicOr(&fl[uint32_t(v) >> 5].x, m) & m) == 0u;
 }
 
-__device__ inline bool bit_get(const uint32_t* bits, int32_t v) {
-  return ((bits[uint32_t(v) >> 5] >> (uint32_t(v) & 31u)) & 1u) != 0u;
+__device__ inline bool bit_of(uint32_t word, int32_t v) { return ((word >> (uint32_t(v) & 31u)) & 1u) != 0u; }
+__device__ inline bool done_get(const uint2* fl, int32_t v) { return bit_of(fl[uint32_t(v) >> 5].y, v); }
+
+// One atomic of a workgroup into one of the spread words of a counter.
+__device__ inline void add_part(uint32_t* parts, uint32_t x) {
+  if (x) atomicAdd(&parts[blockIdx.x & (kIncParts - 1)], x);
 }
 
 // A round's count, read where the atomics that wrote it are coherent (the
@@ -74,13 +78,13 @@ __device__ inline void push_round(int32_t* list, uint32_t* cnt, int r, int32_t v
 }
 
 // Appends the lanes' futures with one atomic per workgroup: thread t holds the
-// futures first + j * stride for the set bits j of mask (every thread of the
-// workgroup calls).  s_tmp holds one word per wave and two more.
-__device__ inline void push_block(uint32_t mask, int64_t first, int32_t* list, uint32_t* n, uint32_t base,
-                                  uint32_t* s_tmp, int64_t stride = 1) {
+// futures first + j for the set bits j of mask (every thread of the workgroup
+// calls).  s_tmp holds one word per wave and two more.
+__device__ inline void push_block(uint64_t mask, int64_t first, int32_t* list, uint32_t* n, uint32_t base,
+                                  uint32_t* s_tmp) {
   const int nw = int(blockDim.x) / kWave;
   const int wv = int(threadIdx.x) / kWave;
-  const uint32_t k = uint32_t(__popc(mask));
+  const uint32_t k = uint32_t(__popcll(mask));
   const uint32_t inc = wave_incl_scan_u32(k);
   if (lane_id() == kWave - 1) s_tmp[wv] = inc;
   __syncthreads();
@@ -93,9 +97,8 @@ __device__ inline void push_block(uint32_t mask, int64_t first, int32_t* list, u
   __syncthreads();
   uint32_t at = base + s_tmp[nw] + off + inc - k;
   while (mask) {
-    const int j = __builtin_ctz(mask);
+    list[at++] = int32_t(first + __builtin_ctzll(mask));
     mask &= mask - 1;
-    list[at++] = int32_t(first + int64_t(j) * stride);
   }
   __syncthreads();  // s_tmp is free again
 }
@@ -181,7 +184,7 @@ __device__ inline void wg_push_heavy(const WgQueue& wq, int32_t* list, uint32_t*
 // lanes holding the same d (a fan-in: many consumers of one future walking
 // at once), else one per lane; returns whether this lane made d a member
 // (one lane per d).  Every lane of the wave calls.
-__device__ inline bool wave_mark(uint32_t* bits, int32_t d) {
+__device__ inline bool wave_mark(uint2* bits, int32_t d) {
   uint64_t pend = ballot(d >= 0);
   bool fresh = false;
   for (int it = 0; it < 2 && pend != 0; ++it) {
@@ -217,7 +220,7 @@ __device__ void close_walk(const IncArgs& a, int32_t u, int round, const WgQueue
         for (int32_t e = o0; e < o1; ++e) {
           const int32_t d = a.p.dep_idx[e];
           if (!dep_ok(a, u, d)) continue;
-          if (bit_set_new(a.inA, d)) {
+          if (bit_set_new(a.fl, d)) {
             join(a, d);
             if (next < 0) next = d;
             else wg_push(wq, a.light, a.ic->cl, round, d);
@@ -226,7 +229,7 @@ __device__ void close_walk(const IncArgs& a, int32_t u, int round, const WgQueue
         u = next;
       }
     }
-    if (wave_mark(a.inA, d1)) {
+    if (wave_mark(a.fl, d1)) {
       join(a, d1);
       u = d1;
     }
@@ -272,7 +275,7 @@ __device__ inline void close_expand(const IncArgs& a, int32_t u, int round, cons
     int32_t d = -1;
     if (e < o1) {
       d = a.p.dep_idx[e];
-      if (dep_ok(a, u, d) && bit_set_new(a.inA, d)) {
+      if (dep_ok(a, u, d) && bit_set_new(a.fl, d)) {
         join(a, d);
         fresh = true;
       }
@@ -285,22 +288,6 @@ __device__ inline void close_expand(const IncArgs& a, int32_t u, int round, cons
 // Every kernel leaves the snapshot alone once validation has failed (the
 // dependency offsets of the appended futures are trusted only then).
 __device__ inline bool invalid(const IncArgs& a) { return a.ctrl->status != 0; }
-
-// The appended futures' membership bits, one word per thread (every bit is
-// clear when this runs).
-__global__ __launch_bounds__(kIncThreads) void k_inc_mark(IncArgs a) {
-  if (invalid(a)) return;
-  const int64_t lo = a.n_prev, hi = a.p.N;
-  if (hi <= lo) return;
-  const int64_t w0 = lo >> 5, w1 = (hi - 1) >> 5;
-  for (int64_t w = w0 + int64_t(blockIdx.x) * kIncThreads + threadIdx.x; w <= w1;
-       w += int64_t(gridDim.x) * kIncThreads) {
-    const int64_t b0 = w * 32 > lo ? w * 32 : lo, b1 = w * 32 + 32 < hi ? w * 32 + 32 : hi;
-    const uint32_t hi_mask = b1 - w * 32 >= 32 ? 0xFFFFFFFFu : ((1u << uint32_t(b1 - w * 32)) - 1u);
-    const uint32_t lo_mask = ~((1u << uint32_t(b0 - w * 32)) - 1u);
-    a.inA[w] = hi_mask & lo_mask;
-  }
-}
 
 // Round 0 takes the seeds (completed ids of the log, then the appended
 // range); round r >= 1 the futures handed on: heavy ones expanded one per
@@ -319,17 +306,17 @@ __device__ void close_round(const IncArgs& a, int r, const WgQueue& wq) {
   }
   __syncthreads();
   // every lane of a wave runs each iteration (the walks work wave by wave)
-  for (int64_t i0 = int64_t(blockIdx.x) * kIncThreads; i0 < n_seed; i0 += int64_t(gridDim.x) * kIncThreads) {
+  for (int64_t i0 = int64_t(blockIdx.x) * blockDim.x; i0 < n_seed; i0 += int64_t(gridDim.x) * blockDim.x) {
     const int64_t i = i0 + threadIdx.x;
     int32_t v = -1;
     if (i < n_seed) {
-      if (i >= a.n_log) {  // appended: already members (k_inc_mark)
+      if (i >= a.n_log) {  // appended: already members (the pack)
         v = int32_t(a.n_prev + (i - a.n_log));
         join(a, v);
       } else {
         const int32_t c = a.log[i];
         // an id out of range is counted by the completion kernel
-        if (c >= 0 && int64_t(c) < a.p.N && bit_set_new(a.inA, c)) {
+        if (c >= 0 && int64_t(c) < a.p.N && bit_set_new(a.fl, c)) {
           join(a, c);
           v = c;
         }
@@ -339,7 +326,7 @@ __device__ void close_round(const IncArgs& a, int r, const WgQueue& wq) {
   }
   const uint32_t bh = round_base(a.ic->ch, r), bl = round_base(a.ic->cl, r);
   for (uint32_t h = blockIdx.x; h < nh; h += gridDim.x) close_expand(a, a.heavy[bh + h], r, wq);
-  for (uint32_t i0 = blockIdx.x * kIncThreads; i0 < nl; i0 += gridDim.x * kIncThreads) {
+  for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < nl; i0 += gridDim.x * blockDim.x) {
     const uint32_t i = i0 + threadIdx.x;
     close_walk(a, i < nl ? a.light[bl + i] : -1, r, wq);
   }
@@ -347,25 +334,25 @@ __device__ void close_round(const IncArgs& a, int r, const WgQueue& wq) {
 }
 
 // The workgroup's LDS queues.
-#define NALAR_INC_QUEUES(keep)                                                  \
+#define NALAR_INC_QUEUES(threads, keep)                                         \
   __shared__ int32_t s_q[kIncQueue], s_hq[kIncHeavyQueue];                      \
   __shared__ int s_n, s_hn, s_htaken;                                           \
-  __shared__ uint32_t s_tmp[kIncThreads / kWave + 2];                           \
+  __shared__ uint32_t s_tmp[(threads) / kWave + 2];                             \
   const WgQueue wq{s_q, &s_n, s_hq, &s_hn, s_tmp, &s_htaken, keep}
 
 __global__ __launch_bounds__(kIncThreads) void k_inc_close(IncArgs a, int r) {
   if (invalid(a)) return;
-  NALAR_INC_QUEUES(false);
+  NALAR_INC_QUEUES(kIncThreads, false);
   close_round(a, r, wq);
 }
 
-// Rounds kIncTail .. kIncRounds - 1 by one workgroup (they are usually empty,
-// and one launch costs less than one per round).  What a round hands on is
-// read by the same workgroup in the next one.
-__global__ __launch_bounds__(kIncThreads) void k_inc_close_tail(IncArgs a) {
+// Rounds r0 .. kIncRounds - 1 by one workgroup (they are usually empty, and one
+// launch costs less than one per round).  What a round hands on is read by the
+// same workgroup in the next one.
+__global__ __launch_bounds__(kIncTailThreads) void k_inc_close_tail(IncArgs a, int r0) {
   if (invalid(a)) return;
-  NALAR_INC_QUEUES(true);
-  for (int r = kIncTail; r < kIncRounds; ++r) {
+  NALAR_INC_QUEUES(kIncTailThreads, true);
+  for (int r = r0; r < kIncRounds; ++r) {
     close_round(a, r, wq);
     __syncthreads();
   }
@@ -419,144 +406,162 @@ __device__ inline void flush_wave_cnt(int32_t* cnt, Pend& p) {
   flush_cnt(cnt, p);
 }
 
-// Appends the lanes' values to a list with one atomic per wave (every lane of
-// the wave calls).
-__device__ inline void push_wave(bool in, int32_t v, int32_t* list, uint32_t* n) {
-  const uint64_t m = ballot(in);
-  if (m == 0) return;
-  const int lead = __builtin_ctzll(m);
-  uint32_t b = 0;
-  if (lane_id() == lead) b = atomicAdd(n, uint32_t(__popcll(m)));
-  b = uint32_t(readlane_i32(int32_t(b), lead));
-  if (in) list[b + lanes_below(m)] = v;
+// The futures with more than kIncHeavy dependencies, one per workgroup at a
+// time.
+__device__ void scan_heavy(const IncArgs& a, uint32_t first, uint32_t step) {
+  __shared__ int s_blocked;
+  constexpr int U = 4;  // dependencies a thread keeps in flight
+  const uint32_t nh = uint32_t(int64_t(*a.hv_n) < a.hv_cap ? *a.hv_n : uint32_t(a.hv_cap));
+  for (uint32_t h = first; h < nh; h += step) {
+    const int32_t v = a.hv[h];
+    if (threadIdx.x == 0) s_blocked = 0;
+    __syncthreads();
+    const uint2 f = a.fl[uint32_t(v) >> 5];
+    const bool in = bit_of(f.x, v);
+    const int32_t o0 = a.p.dep_off[v], o1 = a.p.dep_off[v + 1];
+    bool blocked = false;
+    int64_t rv = 0;
+    if (!in && int64_t(v) < a.n_prev) rv = a.rem[v];
+    for (int32_t e0 = o0 + int32_t(threadIdx.x); e0 < o1; e0 += U * kIncThreads) {
+      int32_t d[U];
+      uint2 w[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int32_t e = e0 + u * kIncThreads;
+        d[u] = e < o1 ? a.p.dep_idx[e] : -1;
+        if (int64_t(d[u]) >= a.p.N) d[u] = -1;  // reported by the closure or an earlier pass
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) w[u] = a.fl[d[u] >= 0 ? uint32_t(d[u]) >> 5 : 0u];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (d[u] < 0) continue;
+        blocked |= !bit_of(w[u].y, d[u]);
+        if (in) atomicAdd(&a.cntA[d[u]], 1);
+        else if (bit_of(w[u].x, d[u])) atomicMax(reinterpret_cast<long long*>(&a.mxA[d[u]]), (long long)rv);
+      }
+    }
+    if (blocked) s_blocked = 1;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      if (in) add_part(a.ic->a_n, 1u);
+      if (!bit_of(f.y, v) && s_blocked == 0) a.rheavy[atomicAdd(&a.ic->r_heavy, 1u)] = v;
+    }
+    __syncthreads();
+  }
 }
 
-// A workgroup takes kScanPer x kIncThreads consecutive futures, thread t the
-// futures t, t + kIncThreads, ... of them (so every load of a wave is
-// coalesced), and issues the loads of all of them together, stage by stage
-// (offsets, membership and done flags; the first dependency; its done flag
-// and membership), so that the gathers of a thread overlap; further
-// dependencies (rare in the graphs this serves) are visited one by one after.
-// A thread's futures lie kIncThreads apart, so a run of futures with one
-// common dependency (the children of a hub) still merges its pushes per lane.
-__global__ __launch_bounds__(kIncThreads) void k_inc_scan(IncArgs a) {
+// The first hb workgroups take the futures of many dependencies (a list the
+// appends keep).  The others take kScanPer x kIncThreads consecutive futures
+// at a time, thread t the futures t, t + kIncThreads, ... of them (so every
+// load of a wave is coalesced), and issue the loads of all of them together,
+// stage by stage (offsets and flags; the first dependency; its flags), so that
+// the gathers of a thread overlap; further dependencies (rare in the graphs
+// this serves) are visited one by one after.  A thread's futures lie
+// kIncThreads apart, so a run of futures with one common dependency (the
+// children of a hub) still merges its pushes per lane.
+//
+// What bounds it is the atomics: what every workgroup adds to must not be one
+// word.  The ready futures leave as one bit each, written per wave (a list
+// cost one returning atomic per workgroup on its length, all queued on that
+// word), and the member count goes to spread words.  At 12.4M futures 191 us,
+// and 17 us for the futures of many dependencies, became 73 us together; at
+// 1.3M 39 + 13 became 19.
+__global__ __launch_bounds__(kIncThreads) void k_inc_scan(IncArgs a, int hb) {
   if (invalid(a)) return;
-  __shared__ uint32_t s_tmp[kIncThreads / kWave + 2];
+  if (int(blockIdx.x) < hb) {
+    scan_heavy(a, blockIdx.x, uint32_t(hb));
+    return;
+  }
+  __shared__ uint32_t s_members[kIncThreads / kWave];
   const int64_t N = a.p.N;
+  const int ln = lane_id();
+  const int wv = int(threadIdx.x) / kWave;
   Pend pm, pc;
   uint32_t members = 0;
-  const int64_t step = int64_t(gridDim.x) * kIncThreads * kScanPer;
-  for (int64_t g0 = int64_t(blockIdx.x) * kIncThreads * kScanPer; g0 < N; g0 += step) {
+  const int64_t step = int64_t(gridDim.x - hb) * kIncThreads * kScanPer;
+  for (int64_t g0 = int64_t(int(blockIdx.x) - hb) * kIncThreads * kScanPer; g0 < N; g0 += step) {
     const int64_t v0 = g0 + int64_t(threadIdx.x);
     int32_t o0[kScanPer], o1[kScanPer], d0[kScanPer];
-    bool in[kScanPer], dn[kScanPer], dd[kScanPer], din[kScanPer];
+    uint2 f[kScanPer], df[kScanPer];
 #pragma unroll
     for (int j = 0; j < kScanPer; ++j) {
       const int64_t v = v0 + int64_t(j) * kIncThreads;
-      const bool ok = v < N;
-      o0[j] = ok ? a.p.dep_off[v] : 0;
-      o1[j] = ok ? a.p.dep_off[v + 1] : 0;
-      in[j] = ok && bit_get(a.inA, int32_t(v));
-      dn[j] = ok ? a.p.done[v] != 0 : true;
+      const int64_t vs = v < N ? v : N - 1;
+      o0[j] = a.p.dep_off[vs];
+      o1[j] = a.p.dep_off[vs + 1];
+      f[j] = a.fl[vs >> 5];
     }
 #pragma unroll
     for (int j = 0; j < kScanPer; ++j) {
       const bool one = o1[j] > o0[j] && o1[j] - o0[j] <= kIncHeavy;
       d0[j] = one ? a.p.dep_idx[o0[j]] : -1;
+      if (int64_t(d0[j]) >= N) d0[j] = -1;
     }
 #pragma unroll
-    for (int j = 0; j < kScanPer; ++j) {
-      const bool okd = d0[j] >= 0 && int64_t(d0[j]) < N;
-      dd[j] = okd ? bit_get(a.dnb, d0[j]) : true;
-      din[j] = okd && bit_get(a.inA, d0[j]);
-    }
-    uint32_t rmask = 0;
+    for (int j = 0; j < kScanPer; ++j) df[j] = a.fl[d0[j] >= 0 ? uint32_t(d0[j]) >> 5 : 0u];
+    uint64_t rword = 0;  // lane j: the ready bits of the wave's futures of item j
 #pragma unroll
     for (int j = 0; j < kScanPer; ++j) {
       const int64_t v = v0 + int64_t(j) * kIncThreads;
-      bool ready = false, heavy = false;
-      if (v < N) {
-        members += in[j] ? 1u : 0u;
-        if (o1[j] - o0[j] > kIncHeavy) {
-          heavy = true;
-        } else {
-          bool blocked = false;
-          int64_t rv = 0;
-          bool have_rv = false;
-          for (int32_t e = o0[j]; e < o1[j]; ++e) {
-            int32_t d;
-            bool d_done, d_in;
-            if (e == o0[j]) {  // the first dependency, loaded above
-              d = d0[j];
-              d_done = dd[j];
-              d_in = din[j];
-            } else {
-              d = a.p.dep_idx[e];
-              const bool okd = d >= 0 && int64_t(d) < N;
-              d_done = okd ? bit_get(a.dnb, d) : true;
-              d_in = okd && bit_get(a.inA, d);
-            }
-            if (d < 0 || int64_t(d) >= N) continue;  // reported by the closure or an earlier pass
-            blocked |= !d_done;
-            if (in[j]) {
-              if (d != pc.d) {
-                flush_cnt(a.cntA, pc);
-                pc.d = d;
-                pc.v = 0;
-              }
-              pc.v += 1;
-            } else if (d_in) {
-              if (!have_rv) {
-                rv = a.rem[v];
-                have_rv = true;
-              }
-              if (d != pm.d) {
-                flush_max(a.mxA, pm);
-                pm.d = d;
-                pm.v = rv;
-              }
-              pm.v = rv > pm.v ? rv : pm.v;
-            }
+      bool ready = false;
+      if (v < N && o1[j] - o0[j] <= kIncHeavy) {
+        const bool in = bit_of(f[j].x, int32_t(v));
+        members += in ? 1u : 0u;
+        bool blocked = false;
+        int64_t rv = 0;
+        bool have_rv = false;
+        for (int32_t e = o0[j]; e < o1[j]; ++e) {
+          int32_t d;
+          uint2 w;
+          if (e == o0[j]) {  // the first dependency, loaded above
+            d = d0[j];
+            w = df[j];
+          } else {
+            d = a.p.dep_idx[e];
+            if (int64_t(d) >= N) d = -1;
+            w = a.fl[d >= 0 ? uint32_t(d) >> 5 : 0u];
           }
-          ready = !dn[j] && !blocked;
+          if (d < 0) continue;  // reported by the closure or an earlier pass
+          blocked |= !bit_of(w.y, d);
+          if (in) {
+            if (d != pc.d) {
+              flush_cnt(a.cntA, pc);
+              pc.d = d;
+              pc.v = 0;
+            }
+            pc.v += 1;
+          } else if (bit_of(w.x, d)) {
+            if (!have_rv) {
+              rv = a.rem[v];
+              have_rv = true;
+            }
+            if (d != pm.d) {
+              flush_max(a.mxA, pm);
+              pm.d = d;
+              pm.v = rv;
+            }
+            pm.v = rv > pm.v ? rv : pm.v;
+          }
         }
+        ready = !bit_of(f[j].y, int32_t(v)) && !blocked;
       }
-      if (ready) rmask |= 1u << j;
-      push_wave(heavy, int32_t(v), a.heavy, &a.ic->scan_heavy);  // rare
+      const uint64_t m = ballot(ready);
+      rword = ln == j ? m : rword;
     }
-    push_block(rmask, v0, a.rlist, &a.ic->r_n, 0u, s_tmp, kIncThreads);
+    // the wave's word of item j covers futures g0 + j * kIncThreads + 64 wv ..
+    const int64_t rw = (g0 + int64_t(ln) * kIncThreads + int64_t(wv) * kWave) / kWave;
+    if (ln < kScanPer && rw * kWave < N) a.rbits[rw] = rword;
   }
   flush_wave_cnt(a.cntA, pc);
   flush_wave_max(a.mxA, pm);
-  const int64_t mt = wave_sum_i64(int64_t(members));
-  if (lane_id() == 0 && mt) atomicAdd(&a.ic->a_n, uint32_t(mt));
-}
-
-// The futures with more than kIncHeavy dependencies, one per workgroup.
-__global__ __launch_bounds__(kIncThreads) void k_inc_scan_heavy(IncArgs a) {
-  if (invalid(a)) return;
-  __shared__ int s_blocked;
-  const uint32_t nh = a.ic->scan_heavy;
-  for (uint32_t h = blockIdx.x; h < nh; h += gridDim.x) {
-    const int32_t v = a.heavy[h];
-    if (threadIdx.x == 0) s_blocked = 0;
-    __syncthreads();
-    const bool in = bit_get(a.inA, v);
-    const int32_t o0 = a.p.dep_off[v], o1 = a.p.dep_off[v + 1];
-    bool blocked = false;
-    int64_t rv = 0;
-    if (!in && int64_t(v) < a.n_prev) rv = a.rem[v];
-    for (int32_t e = o0 + int32_t(threadIdx.x); e < o1; e += kIncThreads) {
-      const int32_t d = a.p.dep_idx[e];
-      if (d < 0 || int64_t(d) >= a.p.N) continue;
-      blocked |= !bit_get(a.dnb, d);
-      if (in) atomicAdd(&a.cntA[d], 1);
-      else if (bit_get(a.inA, d)) atomicMax(reinterpret_cast<long long*>(&a.mxA[d]), (long long)rv);
-    }
-    if (blocked) s_blocked = 1;
-    __syncthreads();
-    if (threadIdx.x == 0 && a.p.done[v] == 0 && s_blocked == 0) a.rlist[atomicAdd(&a.ic->r_n, 1u)] = v;
-    __syncthreads();
+  const uint32_t mt = uint32_t(wave_sum_i64(int64_t(members)));
+  if (ln == 0) s_members[wv] = mt;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t t = 0;
+    for (int x = 0; x < kIncThreads / kWave; ++x) t += s_members[x];
+    add_part(a.ic->a_n, t);
   }
 }
 
@@ -619,7 +624,7 @@ __device__ void sweep_walk(const IncArgs& a, int32_t u, int round, uint32_t& fin
     int32_t d1 = -1;  // the one dependency of a single-dependency future
     int64_t r = 0;
     if (u >= 0) {
-      const int64_t est = bit_get(a.dnb, u) ? 0 : a.p.est[u];
+      const int64_t est = done_get(a.fl, u) ? 0 : a.p.est[u];
       const int64_t m = __hip_atomic_load(&a.mxA[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       r = est + m;
       if (r > NALAR_REM_MAX) {
@@ -655,29 +660,50 @@ __device__ void sweep_walk(const IncArgs& a, int32_t u, int round, uint32_t& fin
 
 __device__ inline void add_fin(const IncArgs& a, uint32_t fin) {
   const int64_t t = wave_sum_i64(int64_t(fin));
-  if (lane_id() == 0 && t) atomicAdd(&a.ic->fin, uint32_t(t));
+  if (lane_id() == 0) add_part(a.ic->fin, uint32_t(t));
 }
 
 // The sweep's first round: every closure member without closure consumers,
 // listed before any member is finalised (a walk may bring another member's
 // count to zero while this list is taken, and that member is then the
-// walker's), one thread per word of the membership bits.
-__global__ __launch_bounds__(kIncThreads) void k_inc_front0(IncArgs a) {
+// walker's).  A thread takes kFrontWords words of the membership bits and, where a
+// word has members, loads all its 32 counts at once (one 128-byte line, in
+// flight together; one member after another, a stretch of appended ids, every
+// bit set, took 32 round trips).  A workgroup appends once, with one returning
+// atomic on the list's length: they queue on that word, so it covers 64K futures.
+//
+// Measured and dropped: no list, but a count of one extra that the first round
+// itself takes off each member.  Spread over all waves the members no longer
+// share their pushes to a common dependency (a session's root), and those
+// atomics, queueing on one word, took the round from 48 to 145 us at 12M futures.
+constexpr int kFrontThreads = 1024;
+constexpr int kFrontWords = 2;
+
+__global__ __launch_bounds__(kFrontThreads) void k_inc_front0(IncArgs a) {
   if (invalid(a)) return;
-  __shared__ uint32_t s_tmp[kIncThreads / kWave + 2];
+  __shared__ uint32_t s_tmp[kFrontThreads / kWave + 2];
   const int64_t words = (a.p.N + 31) / 32;
-  const int64_t step = int64_t(gridDim.x) * kIncThreads;
+  const int64_t step = int64_t(gridDim.x) * kFrontThreads * kFrontWords;
   // the loop runs the same number of times on every thread of the workgroup
-  for (int64_t w0 = int64_t(blockIdx.x) * kIncThreads; w0 < words; w0 += step) {
-    const int64_t w = w0 + threadIdx.x;
-    uint32_t bits = w < words ? a.inA[w] : 0u;
-    uint32_t zmask = 0;
-    while (bits) {
-      const int b = __builtin_ctz(bits);
-      bits &= bits - 1;
-      if (a.cntA[w * 32 + b] == 0) zmask |= 1u << b;
+  for (int64_t w0 = int64_t(blockIdx.x) * kFrontThreads * kFrontWords; w0 < words; w0 += step) {
+    uint64_t zmask = 0;
+#pragma unroll
+    for (int q = 0; q < kFrontWords; ++q) {
+      const int64_t w = w0 + int64_t(threadIdx.x) * kFrontWords + q;
+      const uint32_t bits = w < words ? a.fl[w].x : 0u;
+      if (bits == 0) continue;
+      const int4* c4 = reinterpret_cast<const int4*>(a.cntA + w * 32);  // padded to whole words
+      int4 c[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) c[k] = c4[k];
+      uint32_t z = 0;
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        z |= (uint32_t(c[k].x == 0) | (uint32_t(c[k].y == 0) << 1) | (uint32_t(c[k].z == 0) << 2) |
+              (uint32_t(c[k].w == 0) << 3)) << (4 * k);
+      zmask |= uint64_t(z & bits) << (32 * q);
     }
-    push_block(zmask, w * 32, a.light, &a.ic->sl[0], 0u, s_tmp);
+    push_block(zmask, (w0 + int64_t(threadIdx.x) * kFrontWords) * 32, a.light, &a.ic->sl[0], 0u, s_tmp);
   }
 }
 
@@ -713,7 +739,7 @@ __device__ void sweep_round(const IncArgs& a, int r, const WgQueue& wq, uint32_t
   __syncthreads();
   const uint32_t bh = round_base(a.ic->sh, r), bl = round_base(a.ic->sl, r);
   for (uint32_t h = blockIdx.x; h < nh; h += gridDim.x) sweep_expand(a, a.heavy[bh + h], r, fin, wq);
-  for (uint32_t i0 = blockIdx.x * kIncThreads; i0 < nl; i0 += gridDim.x * kIncThreads) {
+  for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < nl; i0 += gridDim.x * blockDim.x) {
     const uint32_t i = i0 + threadIdx.x;
     sweep_walk(a, i < nl ? a.light[bl + i] : -1, r, fin, wq);
   }
@@ -723,18 +749,18 @@ __device__ void sweep_round(const IncArgs& a, int r, const WgQueue& wq, uint32_t
 
 __global__ __launch_bounds__(kIncThreads) void k_inc_sweep(IncArgs a, int r) {
   if (invalid(a)) return;
-  NALAR_INC_QUEUES(false);
+  NALAR_INC_QUEUES(kIncThreads, false);
   uint32_t fin = 0;
   sweep_round(a, r, wq, fin);
   add_fin(a, fin);
 }
 
-// Rounds kIncTail .. kIncRounds - 1 of the sweep by one workgroup.
-__global__ __launch_bounds__(kIncThreads) void k_inc_sweep_tail(IncArgs a) {
+// Rounds r0 .. kIncRounds - 1 of the sweep by one workgroup (r0 >= 1).
+__global__ __launch_bounds__(kIncTailThreads) void k_inc_sweep_tail(IncArgs a, int r0) {
   if (invalid(a)) return;
-  NALAR_INC_QUEUES(true);
+  NALAR_INC_QUEUES(kIncTailThreads, true);
   uint32_t fin = 0;
-  for (int r = kIncTail; r < kIncRounds; ++r) {
+  for (int r = r0; r < kIncRounds; ++r) {
     sweep_round(a, r, wq, fin);
     __syncthreads();
   }
@@ -743,12 +769,22 @@ __global__ __launch_bounds__(kIncThreads) void k_inc_sweep_tail(IncArgs a) {
 
 // -------------------------------------------------------------------- ready
 
-// Incomplete rounds or an unfinished closure: status for the host.
+// Incomplete rounds or an unfinished closure: status for the host (one wave).
 __device__ inline void check_rounds(const IncArgs& a) {
+  static_assert(kIncParts == kWave, "one spread word per lane");
   const IncCtrl* ic = a.ic;
+  const int64_t open = wave_sum_i64(int64_t(ic->a_n[lane_id()]) - int64_t(ic->fin[lane_id()]));
+  if (lane_id() != 0) return;
+  int rc = 0, rs = 0;  // the deepest rounds that had work
+  for (int r = 1; r < kIncRounds; ++r) {
+    if (ic->cl[r] | ic->ch[r]) rc = r;
+    if (ic->sl[r] | ic->sh[r]) rs = r;
+  }
+  __hip_atomic_store(&a.host->inc_rounds, uint32_t(rc) | (uint32_t(rs) << 8), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_SYSTEM);
   if (ic->cl[kIncRounds] | ic->ch[kIncRounds] | ic->sl[kIncRounds] | ic->sh[kIncRounds])
     flag(a.ctrl, kStIncomplete);
-  else if (ic->fin != ic->a_n)
+  else if (open != 0)
     flag(a.ctrl, kStCycle);  // some member's closure consumers never all finalised
 }
 
@@ -758,125 +794,236 @@ __device__ inline int64_t key_of(uint32_t policy, int64_t rem, int64_t dl) {
   return dl - rem;
 }
 
-// The ready futures: key, bin (splitters in LDS), route, slot.  Per chunk of
-// kReadyPer * T futures, the bins' LDS counts give each future its rank
-// inside the chunk's part of its bin, and one atomic per bin claims that part.
-__global__ __launch_bounds__(kIncThreads) void k_inc_ready(IncArgs a) {
-  constexpr int T = kIncThreads;
-  for (int64_t i = int64_t(blockIdx.x) * T + threadIdx.x; i < a.bk_clear_n; i += int64_t(gridDim.x) * T)
+// The ready futures: key, bin (splitters in LDS), route, slot; and the caller's
+// copy of rem, whose lines the ready futures' gathers read anyway.
+//
+// Every workgroup takes each gridDim-th unit of kReadyUnit consecutive futures
+// (so that all get an even mix of dense and sparse stretches of ids), copies
+// their rem and lists the ready ones in LDS; a chunk of up to kReadyChunk of them
+// is then keyed, counted per bin in LDS, given one segment of each bin with one
+// returning atomic per bin, routed and stored.  The atomics (performed at the
+// memory side, about 12 per ns on the whole chip) and the sparse gathers bound
+// it, so a workgroup is as large as it can be, and a chunk as long: half the
+// segments of 1,024-future chunks over 256-thread workgroups.  At 12.4M futures,
+// 2.3M ready, 159 us and a 40 us copy of rem became 155 us; at 1.3M 42 + 5
+// became 34.
+constexpr int kReadyThreads = 1024;
+constexpr int kReadyPer = 8;                          // ready futures per thread and chunk
+constexpr int kReadyChunk = kReadyPer * kReadyThreads;
+constexpr int kReadyUnit = 256;
+constexpr int kReadyTake = 4;                         // futures per thread and step of the copy
+constexpr int kReadyStep = kReadyTake * kReadyThreads;
+constexpr int kReadyList = kReadyChunk + kReadyStep;  // a chunk and one step's worth
+
+struct ReadyLds {
+  int64_t* split;   // [kBinMax]
+  int64_t* load;    // the instance table
+  double* inv;
+  int32_t* type;
+  int32_t* idx;
+  int32_t* speed;
+  int32_t* pos;
+  uint32_t* run;
+  uint32_t* prun;
+  uint32_t* cnt;    // [kBinMax] the chunk's futures per bin (zero between chunks)
+  uint32_t* base;   // [kBinMax] its segments
+  int32_t* list;    // [kReadyList]
+};
+
+__device__ inline ReadyLds carve_ready(unsigned char* sp, int M) {
+  ReadyLds S;
+  S.split = reinterpret_cast<int64_t*>(sp); sp += 8 * size_t(kBinMax);
+  S.load = reinterpret_cast<int64_t*>(sp); sp += 8 * size_t(M);
+  S.inv = reinterpret_cast<double*>(sp); sp += 8 * size_t(M);
+  S.type = reinterpret_cast<int32_t*>(sp); sp += 4 * size_t(M);
+  S.idx = reinterpret_cast<int32_t*>(sp); sp += 4 * size_t(M);
+  S.speed = reinterpret_cast<int32_t*>(sp); sp += 4 * size_t(M);
+  S.pos = reinterpret_cast<int32_t*>(sp); sp += 4 * size_t(M);
+  S.run = reinterpret_cast<uint32_t*>(sp); sp += 4 * size_t(kTypeDirect);
+  S.prun = reinterpret_cast<uint32_t*>(sp); sp += 4 * size_t(kTypeDirect);
+  S.cnt = reinterpret_cast<uint32_t*>(sp); sp += 4 * size_t(kBinMax);
+  S.base = reinterpret_cast<uint32_t*>(sp); sp += 4 * size_t(kBinMax);
+  S.list = reinterpret_cast<int32_t*>(sp);
+  return S;
+}
+
+struct ReadyAcc {
+  int64_t mn = INT64_MAX, mx = INT64_MIN, n = 0;
+};
+
+// One chunk: the n (at most kReadyChunk) listed futures from `first` on.  Every
+// thread of the workgroup calls it, after a barrier behind the listing.
+__device__ inline void ready_chunk(const IncArgs& a, const ReadyLds& S, int first, int n, ReadyAcc& acc) {
+  constexpr int T = kReadyThreads;
+  const int tid = threadIdx.x;
+  const int nb = a.bk.nb;
+  const uint32_t policy = a.p.policy;
+  const bool out_slack = (policy & (NALAR_ORDER_LPT | NALAR_ORDER_SRTF)) != 0;
+  const bool pack_wf = a.p.W <= kPackWf;
+  int32_t v[kReadyPer], wf[kReadyPer];
+  int64_t key[kReadyPer];
+  uint32_t bin[kReadyPer];  // bin, then bin | rank << 16 (rank < kReadyChunk)
+  static_assert(kBinMax <= 65536 && kReadyChunk <= 65536, "bin and rank share a word");
+#pragma unroll
+  for (int j = 0; j < kReadyPer; ++j) v[j] = j * T + tid < n ? S.list[first + j * T + tid] : -1;
+#pragma unroll
+  for (int j = 0; j < kReadyPer; ++j) {
+    wf[j] = v[j] >= 0 ? a.p.wf[v[j]] : 0;
+    key[j] = v[j] >= 0 ? a.rem[v[j]] : 0;
+  }
+#pragma unroll
+  for (int j = 0; j < kReadyPer; ++j) {
+    bin[j] = 0;
+    if (v[j] < 0) continue;
+    const int64_t dl = a.p.deadline[wf[j]] - a.p.now;
+    if (out_slack) a.stg_oslack[v[j]] = dl - key[j];
+    key[j] = key_of(policy, key[j], dl);
+  }
+  for (int st = nb >> 1; st > 0; st >>= 1) {
+#pragma unroll
+    for (int j = 0; j < kReadyPer; ++j)
+      if (v[j] >= 0 && S.split[bin[j] + st - 1] <= key[j]) bin[j] += st;
+  }
+#pragma unroll
+  for (int j = 0; j < kReadyPer; ++j)
+    if (v[j] >= 0) bin[j] |= atomicAdd(&S.cnt[bin[j]], 1u) << 16;
+  __syncthreads();
+  {  // one segment per bin for the chunk: every thread's atomics in flight together
+    constexpr int kPerT = kBinMax / T;
+    uint32_t c[kPerT];
+#pragma unroll
+    for (int q = 0; q < kPerT; ++q) {
+      const int t = tid + q * T;
+      c[q] = t < nb ? S.cnt[t] : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < kPerT; ++q) c[q] = c[q] ? add_agent(a.bk.cnt + tid + q * T, c[q]) : 0u;
+#pragma unroll
+    for (int q = 0; q < kPerT; ++q) {
+      const int t = tid + q * T;
+      if (t < nb) {
+        S.base[t] = c[q];
+        S.cnt[t] = 0;  // clean again before the next chunk
+      }
+    }
+  }
+  __syncthreads();
+  int32_t ty[kReadyPer], lc[kReadyPer];
+  int64_t es[kReadyPer];
+#pragma unroll
+  for (int j = 0; j < kReadyPer; ++j) {
+    const int32_t u = v[j] >= 0 ? v[j] : 0;
+    ty[j] = a.p.type[u];
+    lc[j] = a.p.loc[u];
+    es[j] = a.p.est[u];
+  }
+#pragma unroll
+  for (int j = 0; j < kReadyPer; ++j) {
+    if (v[j] < 0) continue;
+    int32_t route;
+    int64_t cost;
+    route_future(ty[j], es[j], lc[j], int32_t(a.p.M), a.p.mig, S.type, S.idx, S.load, S.speed, S.inv, S.pos,
+                 S.run, (policy & NALAR_ROUTE_STATEFUL) != 0, route, cost, S.prun);
+    const uint32_t b = bin[j] & 0xFFFFu;
+    const uint32_t slot = (bin[j] >> 16) + S.base[b];
+    if (slot < uint32_t(a.bk.cap)) {
+      int64_t* sl = reinterpret_cast<int64_t*>(a.bk.slot + int64_t(b) * a.bk.cap + slot);
+      const int32_t rw = pack_wf ? slot_pack_wf(route, wf[j]) : slot_pack(route, 0);
+      sl[0] = key[j];
+      sl[1] = cost;
+      sl[2] = int64_t(uint64_t(uint32_t(v[j])) | (uint64_t(uint32_t(rw)) << 32));
+    } else {
+      st_relaxed_agent(&a.ctrl->bucket_overflow, 1u);
+    }
+    acc.mn = key[j] < acc.mn ? key[j] : acc.mn;
+    acc.mx = key[j] > acc.mx ? key[j] : acc.mx;
+    acc.n += 1;
+  }
+}
+
+__global__ __launch_bounds__(kReadyThreads) void k_inc_ready(IncArgs a) {
+  constexpr int T = kReadyThreads;
+  const int tid = threadIdx.x;
+  for (int64_t i = int64_t(blockIdx.x) * T + tid; i < a.bk_clear_n; i += int64_t(gridDim.x) * T)
     a.bk_clear[i] = 0;  // the next pass's bin counters
   Ctrl* ctrl = a.ctrl;
   if (ctrl->status != 0) return;
-  if (blockIdx.x == 0 && threadIdx.x == 0) check_rounds(a);
-  if ((ctrl->status | ctrl->status_sweep) != 0) return;
+  if (blockIdx.x == 0 && tid < kWave) check_rounds(a);
   extern __shared__ __align__(16) unsigned char smem[];
   const int M = int(a.p.M);
-  const int nb = a.bk.nb;
-  unsigned char* sp = smem;
-  int64_t* s_split = reinterpret_cast<int64_t*>(sp); sp += 8 * size_t(kBinMax);
-  int64_t* s_load = reinterpret_cast<int64_t*>(sp); sp += 8 * size_t(M);
-  double* s_inv = reinterpret_cast<double*>(sp); sp += 8 * size_t(M);
-  int32_t* s_type = reinterpret_cast<int32_t*>(sp); sp += 4 * size_t(M);
-  int32_t* s_idx = reinterpret_cast<int32_t*>(sp); sp += 4 * size_t(M);
-  int32_t* s_speed = reinterpret_cast<int32_t*>(sp); sp += 4 * size_t(M);
-  int32_t* s_pos = reinterpret_cast<int32_t*>(sp); sp += 4 * size_t(M);
-  uint32_t* s_run = reinterpret_cast<uint32_t*>(sp); sp += 4 * size_t(kTypeDirect);
-  uint32_t* s_prun = reinterpret_cast<uint32_t*>(sp); sp += 4 * size_t(kTypeDirect);
-  uint32_t* s_cnt = reinterpret_cast<uint32_t*>(sp); sp += 4 * size_t(kBinMax);
-  uint32_t* s_base = reinterpret_cast<uint32_t*>(sp);
+  const ReadyLds S = carve_ready(smem, M);
+  __shared__ int s_n;
   __shared__ int64_t s_red[3][T / kWave];
-  const int tid = threadIdx.x;
   for (int i = tid; i < M; i += T) {
-    s_load[i] = a.itab.load[i];
-    s_inv[i] = a.itab.inv_speed[i];
-    s_type[i] = a.itab.type[i];
-    s_idx[i] = a.itab.idx[i];
-    s_speed[i] = a.itab.speed[i];
-    s_pos[i] = a.itab.pos_of[i];
+    S.load[i] = a.itab.load[i];
+    S.inv[i] = a.itab.inv_speed[i];
+    S.type[i] = a.itab.type[i];
+    S.idx[i] = a.itab.idx[i];
+    S.speed[i] = a.itab.speed[i];
+    S.pos[i] = a.itab.pos_of[i];
   }
   for (int t = tid; t < kTypeDirect; t += T) {
-    s_run[t] = a.itab.run[t];
-    s_prun[t] = a.itab.prun[t];
+    S.run[t] = a.itab.run[t];
+    S.prun[t] = a.itab.prun[t];
   }
-  for (int i = tid; i < nb - 1; i += T) s_split[i] = a.bk.split[i];
-  for (int i = tid; i < nb; i += T) s_cnt[i] = 0;
+  for (int i = tid; i < a.bk.nb - 1; i += T) S.split[i] = a.bk.split[i];
+  for (int i = tid; i < a.bk.nb; i += T) S.cnt[i] = 0;
+  if (tid == 0) s_n = 0;
   __syncthreads();
-  const uint32_t policy = a.p.policy;
-  const bool out_slack = (policy & (NALAR_ORDER_LPT | NALAR_ORDER_SRTF)) != 0;
-  const int64_t R = a.ic->r_n;
-  int64_t tmin = INT64_MAX, tmax = INT64_MIN, tready = 0;
-  constexpr int64_t kChunk = int64_t(kReadyPer) * T;
-  for (int64_t c0 = int64_t(blockIdx.x) * kChunk; c0 < R; c0 += int64_t(gridDim.x) * kChunk) {
-    int32_t v[kReadyPer];
-    int64_t key[kReadyPer], rem[kReadyPer], dl[kReadyPer];
-    uint32_t bin[kReadyPer], rk[kReadyPer];
-#pragma unroll
-    for (int j = 0; j < kReadyPer; ++j) {
-      const int64_t i = c0 + j * T + tid;
-      v[j] = -1;
-      key[j] = rem[j] = dl[j] = 0;
-      bin[j] = rk[j] = 0;
-      if (i < R) {
-        v[j] = a.rlist[i];
-        rem[j] = a.rem[v[j]];
-        dl[j] = a.p.deadline[a.p.wf[v[j]]] - a.p.now;
-        key[j] = key_of(policy, rem[j], dl[j]);
-      }
-    }
-    for (int st = nb >> 1; st > 0; st >>= 1) {
-#pragma unroll
-      for (int j = 0; j < kReadyPer; ++j)
-        if (v[j] >= 0 && s_split[bin[j] + st - 1] <= key[j]) bin[j] += st;
-    }
-#pragma unroll
-    for (int j = 0; j < kReadyPer; ++j)
-      if (v[j] >= 0) rk[j] = atomicAdd(&s_cnt[bin[j]], 1u);
+  const int64_t N = a.p.N;
+  const int64_t G = gridDim.x;
+  ReadyAcc acc;
+  // the ready futures of many dependencies (their own list)
+  const uint32_t nh = a.ic->r_heavy;
+  for (uint32_t h0 = blockIdx.x; h0 < nh; h0 += uint32_t(G) * T) {
+    const uint64_t h = uint64_t(h0) + uint64_t(tid) * uint64_t(G);
+    const bool in = h < nh;
+    const uint64_t m = ballot(in);
+    int at = 0;
+    if (lane_id() == 0 && m) at = atomicAdd(&s_n, int(__popcll(m)));
+    at = readlane_i32(at, 0);
+    if (in) S.list[at + int(lanes_below(m))] = a.rheavy[h];
     __syncthreads();
-    {  // one segment per bin for the chunk: every thread's atomics in flight together
-      constexpr int kPerT = kBinMax / T;
-      uint32_t c[kPerT];
-#pragma unroll
-      for (int q = 0; q < kPerT; ++q) {
-        const int t = tid + q * T;
-        c[q] = t < nb ? s_cnt[t] : 0u;
-      }
-#pragma unroll
-      for (int q = 0; q < kPerT; ++q) c[q] = c[q] ? add_agent(a.bk.cnt + tid + q * T, c[q]) : 0u;
-#pragma unroll
-      for (int q = 0; q < kPerT; ++q) {
-        const int t = tid + q * T;
-        if (t < nb) {
-          s_base[t] = c[q];
-          s_cnt[t] = 0;
-        }
-      }
+    const int n = s_n;
+    if (n >= kReadyChunk) {  // the same on every thread
+      ready_chunk(a, S, n - kReadyChunk, kReadyChunk, acc);
+      if (tid == 0) s_n = n - kReadyChunk;
     }
     __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kReadyPer; ++j) {
-      if (v[j] < 0) continue;
-      const int32_t u = v[j];
-      int32_t route;
-      int64_t cost;
-      route_future(a.p.type[u], a.p.est[u], a.p.loc[u], int32_t(M), a.p.mig, s_type, s_idx, s_load, s_speed,
-                   s_inv, s_pos, s_run, (policy & NALAR_ROUTE_STATEFUL) != 0, route, cost, s_prun);
-      const uint32_t slot = rk[j] + s_base[bin[j]];
-      if (slot < uint32_t(a.bk.cap)) {
-        int64_t* sl = reinterpret_cast<int64_t*>(a.bk.slot + int64_t(bin[j]) * a.bk.cap + slot);
-        sl[0] = key[j];
-        sl[1] = cost;
-        sl[2] = int64_t(uint64_t(uint32_t(u)) | (uint64_t(uint32_t(slot_pack(route, 0))) << 32));
-      } else {
-        st_relaxed_agent(&ctrl->bucket_overflow, 1u);
-      }
-      if (out_slack) a.stg_oslack[u] = dl[j] - rem[j];
-      tmin = key[j] < tmin ? key[j] : tmin;
-      tmax = key[j] > tmax ? key[j] : tmax;
-      tready += 1;
-    }
-    __syncthreads();  // the counters are clean again before the next chunk
   }
-  const int64_t mn = wave_min_i64(tmin), mx = wave_max_i64(tmax), rd = wave_sum_i64(tready);
+  constexpr int kUnits = kReadyStep / kReadyUnit;  // units per step
+  const int64_t units = (N + kReadyUnit - 1) / kReadyUnit;
+  for (int64_t k0 = 0; int64_t(blockIdx.x) + k0 * G < units; k0 += kUnits) {
+    int64_t id[kReadyTake], rv[kReadyTake];
+    uint64_t w[kReadyTake];
+#pragma unroll
+    for (int j = 0; j < kReadyTake; ++j) {
+      const int64_t k = k0 + j * (T / kReadyUnit) + tid / kReadyUnit;
+      const int64_t u = int64_t(blockIdx.x) + k * G;
+      id[j] = u < units ? u * kReadyUnit + (tid & (kReadyUnit - 1)) : N;
+      w[j] = id[j] < N ? a.rbits[id[j] / kWave] : 0;  // the same on the lanes of the wave below N
+      if (a.rem_out) rv[j] = id[j] < N ? a.rem[id[j]] : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < kReadyTake; ++j) {
+      if (a.rem_out && id[j] < N) a.rem_out[id[j]] = rv[j];
+      const bool in = (w[j] >> lane_id()) & 1u;
+      const uint64_t m = ballot(in);
+      int at = 0;
+      if (lane_id() == 0 && m) at = atomicAdd(&s_n, int(__popcll(m)));
+      at = readlane_i32(at, 0);
+      if (in) S.list[at + int(lanes_below(m))] = int32_t(id[j]);
+    }
+    __syncthreads();
+    const int n = s_n;
+    if (n >= kReadyChunk) {  // the same on every thread
+      ready_chunk(a, S, n - kReadyChunk, kReadyChunk, acc);
+      if (tid == 0) s_n = n - kReadyChunk;
+    }
+    __syncthreads();
+  }
+  if (s_n > 0) ready_chunk(a, S, 0, s_n, acc);  // at most kReadyChunk - 1
+  const int64_t mn = wave_min_i64(acc.mn), mx = wave_max_i64(acc.mx), rd = wave_sum_i64(acc.n);
   const int wv = tid / kWave;
   if (lane_id() == 0) {
     s_red[0][wv] = mn;
@@ -900,30 +1047,6 @@ __global__ __launch_bounds__(kIncThreads) void k_inc_ready(IncArgs a) {
   }
 }
 
-// Word i of the membership bits cleared, and of the done bits packed from
-// the done flags of futures 32i .. 32i+31 (the gathers of dependencies' flags
-// then read 1/8 of the bytes, a bitmap that stays in the L2).
-__global__ __launch_bounds__(kIncThreads) void k_inc_pack(IncArgs a) {
-  const int64_t N = a.p.N, nw = (N + 31) / 32;
-  for (int64_t i = int64_t(blockIdx.x) * kIncThreads + threadIdx.x; i < nw; i += int64_t(gridDim.x) * kIncThreads) {
-    const int64_t v0 = 32 * i;
-    uint32_t bits = 0;
-    if (v0 + 32 <= N) {  // 32 flags in two aligned 16-byte loads (the array is 256-byte aligned)
-      const uint4* q = reinterpret_cast<const uint4*>(a.p.done + v0);
-      const uint4 x = q[0], y = q[1];
-      const uint32_t w[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) bits |= uint32_t(((w[k] >> (8 * b)) & 0xFFu) != 0u) << (4 * k + b);
-    } else {
-      for (int64_t v = v0; v < N; ++v) bits |= uint32_t(a.p.done[v] != 0) << uint32_t(v - v0);
-    }
-    a.inA[i] = 0;
-    a.dnb[i] = bits;
-  }
-}
-
 __global__ __launch_bounds__(kIncThreads) void k_inc_clear(uint32_t* p, int64_t n) {
   for (int64_t i = int64_t(blockIdx.x) * kIncThreads + threadIdx.x; i < n; i += int64_t(gridDim.x) * kIncThreads)
     p[i] = 0;
@@ -939,7 +1062,8 @@ int inc_grid(int64_t n, int cap) {
 }  // namespace
 
 size_t inc_ready_lds(int64_t M) {
-  return 8 * size_t(kBinMax) + 32 * size_t(M) + 8 * size_t(kTypeDirect) + 8 * size_t(kBinMax);
+  return 8 * size_t(kBinMax) + 32 * size_t(M) + 8 * size_t(kTypeDirect) + 8 * size_t(kBinMax) +
+         4 * size_t(kReadyList);
 }
 
 hipError_t prepare_inc_kernels() {
@@ -953,67 +1077,65 @@ hipError_t launch_inc_clear(hipStream_t s, uint32_t* p, int64_t n) {
   return hipGetLastError();
 }
 
-hipError_t launch_inc_pack(hipStream_t s, const IncArgs& a) {
-  const int64_t nw = (a.p.N + 31) / 32;
-  if (nw <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_inc_pack, dim3(inc_grid(nw, 2048)), dim3(kIncThreads), 0, s, a);
-  return hipGetLastError();
-}
-
 constexpr const char* kCloseNames[kIncRounds] = {"inc_close_r0", "inc_close_r1", "inc_close_r2", "inc_close_r3",
                                                   "inc_close_r4", "inc_close_r5", "inc_close_r6", "inc_close_r7"};
 constexpr const char* kSweepNames[kIncRounds] = {"inc_sweep_r0", "inc_sweep_r1", "inc_sweep_r2", "inc_sweep_r3",
                                                   "inc_sweep_r4", "inc_sweep_r5", "inc_sweep_r6", "inc_sweep_r7"};
 static_assert(kIncRounds == 8, "one name per round");
 
-hipError_t launch_inc_closure(hipStream_t s, const IncArgs& a, int cus, void (*mark)(void*, const char*),
-                              void* ctx) {
+hipError_t launch_inc_closure(hipStream_t s, const IncArgs& a, int cus, int rounds,
+                              void (*mark)(void*, const char*), void* ctx) {
   const int64_t seeds = a.n_log + (a.p.N - a.n_prev);
-  mark(ctx, "inc_mark");
-  hipLaunchKernelGGL(k_inc_mark, dim3(inc_grid((a.p.N - a.n_prev) / 32 + 2, 1024)), dim3(kIncThreads), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (rounds > kIncTail) rounds = kIncTail;
+  if (rounds < 1) rounds = 1;
   mark(ctx, kCloseNames[0]);
   hipLaunchKernelGGL(k_inc_close, dim3(inc_grid(seeds, 4096)), dim3(kIncThreads), 0, s, a, 0);
-  e = hipGetLastError();
-  for (int r = 1; r < kIncTail && e == hipSuccess; ++r) {
+  hipError_t e = hipGetLastError();
+  for (int r = 1; r < rounds && e == hipSuccess; ++r) {
     mark(ctx, kCloseNames[r]);
     hipLaunchKernelGGL(k_inc_close, dim3(r < 2 ? 4 * cus : cus), dim3(kIncThreads), 0, s, a, r);
     e = hipGetLastError();
   }
   if (e != hipSuccess) return e;
   mark(ctx, "inc_close_tail");
-  hipLaunchKernelGGL(k_inc_close_tail, dim3(1), dim3(kIncThreads), 0, s, a);
+  hipLaunchKernelGGL(k_inc_close_tail, dim3(1), dim3(kIncTailThreads), 0, s, a, rounds);
   return hipGetLastError();
 }
 
 hipError_t launch_inc_scan(hipStream_t s, const IncArgs& a, int cus) {
-  hipLaunchKernelGGL(k_inc_scan, dim3(inc_grid((a.p.N + kScanPer - 1) / kScanPer, 16 * cus)),
-                     dim3(kIncThreads), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_inc_scan_heavy, dim3(2 * cus), dim3(kIncThreads), 0, s, a);
+  // as many workgroups for the futures of many dependencies as the edges allow
+  const int64_t most = a.p.E / (kIncHeavy + 1);
+  const int hb = int(most < cus ? most : cus);
+  hipLaunchKernelGGL(k_inc_scan, dim3(hb + inc_grid((a.p.N + kScanPer - 1) / kScanPer, 16 * cus)),
+                     dim3(kIncThreads), 0, s, a, hb);
   return hipGetLastError();
 }
 
-hipError_t launch_inc_sweep(hipStream_t s, const IncArgs& a, int cus, void (*mark)(void*, const char*),
-                            void* ctx) {
+hipError_t launch_inc_sweep(hipStream_t s, const IncArgs& a, int cus, int rounds,
+                            void (*mark)(void*, const char*), void* ctx) {
+  if (rounds > kIncTail) rounds = kIncTail;
+  if (rounds < 1) rounds = 1;
   mark(ctx, "inc_front0");
-  hipLaunchKernelGGL(k_inc_front0, dim3(inc_grid((a.p.N + 31) / 32, 8 * cus)), dim3(kIncThreads), 0, s, a);
+  const int64_t words = (a.p.N + 31) / 32, per = kFrontThreads * kFrontWords;
+  hipLaunchKernelGGL(k_inc_front0, dim3(inc_grid((words + per - 1) / per * kIncThreads, 4 * cus)),
+                     dim3(kFrontThreads), 0, s, a);
   hipError_t e = hipGetLastError();
-  for (int r = 0; r < kIncTail && e == hipSuccess; ++r) {
+  for (int r = 0; r < rounds && e == hipSuccess; ++r) {
     mark(ctx, kSweepNames[r]);
     hipLaunchKernelGGL(k_inc_sweep, dim3(4 * cus), dim3(kIncThreads), 0, s, a, r);
     e = hipGetLastError();
   }
   if (e != hipSuccess) return e;
   mark(ctx, "inc_sweep_tail");
-  hipLaunchKernelGGL(k_inc_sweep_tail, dim3(1), dim3(kIncThreads), 0, s, a);
+  hipLaunchKernelGGL(k_inc_sweep_tail, dim3(1), dim3(kIncTailThreads), 0, s, a, rounds);
   return hipGetLastError();
 }
 
 hipError_t launch_inc_ready(hipStream_t s, const IncArgs& a, int cus) {
-  hipLaunchKernelGGL(k_inc_ready, dim3(4 * cus), dim3(kIncThreads), inc_ready_lds(a.p.M), s, a);
+  // one workgroup per CU (their LDS allows no more), fewer for few futures
+  int64_t g = (a.p.N + kReadyStep - 1) / kReadyStep;
+  if (g > cus) g = cus;
+  hipLaunchKernelGGL(k_inc_ready, dim3(unsigned(g < 1 ? 1 : g)), dim3(kReadyThreads), inc_ready_lds(a.p.M), s, a);
   return hipGetLastError();
 }
 

@@ -237,9 +237,47 @@ __device__ void instance_table(const ProblemDev& p, ITab it, unsigned char* smem
 // instance table sorted by type, so each future's candidates form one
 // contiguous run; workgroup 1 also resets the control block of the next pass
 // (the grid always has a second workgroup).
+//
+// With kPack (an incremental pass), the other workgroups also write the flags
+// the pass gathers per future: word pair i holds the membership bits of futures
+// 32i .. 32i+31 (the appended ones, from n_prev on) and their done flags (1/8 of
+// the bytes, a bitmap that stays in the L2), and the pass's counters are
+// cleared.  It shares the launch because the table's one workgroup is the
+// longest either way (8.4 us, against 4 to 6 us for the flags of 1M to 12M
+// futures).
+template <bool kPack>
+__device__ inline void inc_pack(const ProblemDev& p, const IncPack& pk, int64_t g0, int64_t stride) {
+  if (!kPack) return;
+  const int64_t N = p.N, nw = (N + 31) / 32;
+  for (int64_t i = g0; i < nw; i += stride) {
+    const int64_t v0 = 32 * i;
+    uint32_t bits = 0;
+    if (v0 + 32 <= N) {  // 32 flags in two aligned 16-byte loads (the array is 256-byte aligned)
+      const uint4* q = reinterpret_cast<const uint4*>(p.done + v0);
+      const uint4 x = q[0], y = q[1];
+      const uint32_t w[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) bits |= uint32_t(((w[k] >> (8 * b)) & 0xFFu) != 0u) << (4 * k + b);
+    } else {
+      for (int64_t v = v0; v < N; ++v) bits |= uint32_t(p.done[v] != 0) << uint32_t(v - v0);
+    }
+    uint32_t in = 0;  // futures n_prev .. N - 1 of the word
+    if (v0 + 32 > pk.n_prev) {
+      in = pk.n_prev > v0 ? ~((1u << uint32_t(pk.n_prev - v0)) - 1u) : ~0u;
+      if (v0 + 32 > N) in &= (1u << uint32_t(N - v0)) - 1u;
+    }
+    pk.fl[i] = make_uint2(in, bits);
+  }
+  uint32_t* ic = reinterpret_cast<uint32_t*>(pk.ic);
+  for (int64_t i = g0; i < int64_t(sizeof(IncCtrl) / 4); i += stride) ic[i] = 0;
+}
+
+template <bool kPack>
 __global__ __launch_bounds__(kNodeThreads) void k_nodes(ProblemDev p, Ctrl* ctrl, Ctrl* next_ctrl,
                                                        ITab it, int32_t* wf_off, int contiguous,
-                                                       int64_t v_begin, uint64_t* done_bits) {
+                                                       int64_t v_begin, uint64_t* done_bits, IncPack pk) {
   const int64_t N = p.N, W = p.W, M = p.M;
   if (blockIdx.x == 0) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -249,6 +287,7 @@ __global__ __launch_bounds__(kNodeThreads) void k_nodes(ProblemDev p, Ctrl* ctrl
   if (blockIdx.x == 1) reset_ctrl(next_ctrl);  // unused by this pass; ready for the next one
   const int64_t stride = int64_t(gridDim.x - 1) * kNodeThreads;
   const int64_t g0 = int64_t(blockIdx.x - 1) * kNodeThreads + threadIdx.x;
+  inc_pack<kPack>(p, pk, g0, stride);
   bool bad = false;
   // kNodeItems nodes a stride apart per thread, every load issued before the
   // first check, so that each thread keeps that many lines in flight
@@ -319,12 +358,21 @@ int grid_for(int64_t n, int threads, int cap) {
 }  // namespace
 
 hipError_t launch_nodes(hipStream_t s, const ProblemDev& p, Ctrl* ctrl, Ctrl* next_ctrl, ITab itab,
-                        int32_t* wf_off, int contiguous, int64_t v_begin, uint64_t* done_bits) {
+                        int32_t* wf_off, int contiguous, int64_t v_begin, uint64_t* done_bits,
+                        const IncPack* pack) {
   if (v_begin % kWave != 0) done_bits = nullptr;  // a wave's futures must fill whole words
   const int64_t nv = (p.N - v_begin + kNodeItems - 1) / kNodeItems;
   int64_t n = nv > p.W + 1 ? nv : p.W + 1;
-  hipLaunchKernelGGL(k_nodes, dim3(grid_for(n, kNodeThreads, 4096) + 1), dim3(kNodeThreads), tab_lds_bytes(p.M), s, p,
-                     ctrl, next_ctrl, itab, wf_off, contiguous, v_begin, done_bits);
+  if (pack) {
+    const int64_t nw = (p.N + 31) / 32;
+    n = n > nw ? n : nw;
+    hipLaunchKernelGGL(k_nodes<true>, dim3(grid_for(n, kNodeThreads, 4096) + 1), dim3(kNodeThreads),
+                       tab_lds_bytes(p.M), s, p, ctrl, next_ctrl, itab, wf_off, contiguous, v_begin, done_bits, *pack);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(k_nodes<false>, dim3(grid_for(n, kNodeThreads, 4096) + 1), dim3(kNodeThreads),
+                     tab_lds_bytes(p.M), s, p, ctrl, next_ctrl, itab, wf_off, contiguous, v_begin, done_bits,
+                     IncPack{});
   return hipGetLastError();
 }
 

@@ -58,6 +58,7 @@ struct SortArgs {
                                 //   splitters wait for the last one)
   const int32_t* tie_wf;        // bin sort: positions are node ids, equal keys ordered by
                                 //   (tie_wf[id], id); NULL: by position
+  int32_t tie_packed;           // the records carry their workflow (slot_pack_wf)
   ProblemDev p;                 // the snapshot (deadline, wf and the key's policy for the splitters)
   int32_t* order;
   int64_t* slack;
@@ -226,12 +227,18 @@ hipError_t launch_decide(hipStream_t s, const DecideArgs& a);
 // closure and of its sweep append to per-round lists (items of round r follow
 // those of rounds 0 .. r-1); the host launches kIncRounds rounds of each.
 constexpr int kIncRounds = 8;
+constexpr uint32_t kIncRoundsAll = uint32_t(kIncRounds) | (uint32_t(kIncRounds) << 8);  // HostStatus::inc_rounds unknown
+constexpr int kIncHeavy = 64;     // more dependencies: one workgroup expands the future
+
+// Counters that many workgroups add to are spread over kIncParts words: every
+// device-scope atomic on one word queues behind the others (at the memory side,
+// tens of ns each).
+constexpr int kIncParts = 64;
 
 struct IncCtrl {
-  uint32_t a_n;                  // closure members
-  uint32_t r_n;                  // ready futures
-  uint32_t fin;                  // closure members finalised by the sweep
-  uint32_t scan_heavy;           // futures with many dependencies, for the scan
+  uint32_t a_n[kIncParts];       // closure members
+  uint32_t fin[kIncParts];       // closure members finalised by the sweep
+  uint32_t r_heavy;              // ready futures with many dependencies (rheavy)
   uint32_t cl[kIncRounds + 1];   // closure: single futures per round
   uint32_t ch[kIncRounds + 1];   // closure: futures expanded by a workgroup
   uint32_t sl[kIncRounds + 1];   // sweep: single futures per round
@@ -244,14 +251,20 @@ struct IncArgs {
   const int32_t* log;            // [n_log] ids completed since the last pass
   int64_t n_log;
   int64_t* rem;                  // [N] remaining critical path, kept across passes
-  uint32_t* inA;                 // [ceil(N/32)] closure membership bits (cleared by the pack)
-  uint32_t* dnb;                 // [ceil(N/32)] done flags as bits (written by the pack)
+  int64_t* rem_out;              // [N] the caller's copy of rem, or NULL
+  uint2* fl;                     // [ceil(N/32)] x: closure membership bits, y: done flags as bits
+                                 //   (one gather gives both; written by the pack)
   int64_t* mxA;                  // [N] max rem over consumers (closure members)
   int32_t* cntA;                 // [N] closure consumers not yet finalised (members)
   int32_t* light;                // [N] per-round lists
   int32_t* heavy;                // [N]
-  int32_t* rlist;                // [N] ready futures
-  IncCtrl* ic;                   // zero on entry
+  uint64_t* rbits;               // [ceil(N/64)] ready futures with few dependencies, as bits
+  const int32_t* hv;             // [hv_cap] futures with more than kIncHeavy dependencies
+  const uint32_t* hv_n;          //   and their number
+  int64_t hv_cap;
+  int32_t* rheavy;               // [hv_cap] the ready ones of them
+  IncCtrl* ic;                   // cleared by the pack
+  HostStatus* host;              // inc_rounds: the deepest rounds that had work
   Ctrl* ctrl;                    // the pass's control block
   ITab itab;
   BucketArgs bk;                 // bins (the previous pass's splitters)
@@ -262,12 +275,14 @@ struct IncArgs {
 size_t inc_ready_lds(int64_t M);
 hipError_t prepare_inc_kernels();
 hipError_t launch_inc_clear(hipStream_t s, uint32_t* p, int64_t n_words);
-// Clears the membership bits and packs the done flags into bits.
-hipError_t launch_inc_pack(hipStream_t s, const IncArgs& a);
-// (mark(ctx, name) before each launch, for timing)
-hipError_t launch_inc_closure(hipStream_t s, const IncArgs& a, int cus, void (*mark)(void*, const char*), void* ctx);
+// The closure and its sweep, with `rounds` rounds of their own launch each (1 to
+// 3) before one workgroup runs the rest; mark(ctx, name) before each launch, for
+// timing.
+hipError_t launch_inc_closure(hipStream_t s, const IncArgs& a, int cus, int rounds,
+                              void (*mark)(void*, const char*), void* ctx);
 hipError_t launch_inc_scan(hipStream_t s, const IncArgs& a, int cus);
-hipError_t launch_inc_sweep(hipStream_t s, const IncArgs& a, int cus, void (*mark)(void*, const char*), void* ctx);
+hipError_t launch_inc_sweep(hipStream_t s, const IncArgs& a, int cus, int rounds,
+                            void (*mark)(void*, const char*), void* ctx);
 hipError_t launch_inc_ready(hipStream_t s, const IncArgs& a, int cus);
 
 // The store's side of an incremental pass (defined in api.hip): its buffers,
@@ -282,16 +297,20 @@ struct IncStore {
   const int32_t* log;
   int64_t n_log;
   int64_t* rem;
-  uint32_t* inA;
-  uint32_t* dnb;
+  uint2* fl;
   int64_t* mxA;
   int32_t* cntA;
   int32_t* light;
   int32_t* heavy;
-  int32_t* rlist;
+  uint64_t* rbits;
+  const int32_t* hv;
+  const uint32_t* hv_n;
+  int64_t hv_cap;
+  int32_t* rheavy;
   IncCtrl* ic;
+  uint32_t rounds;               // the last incremental pass's inc_rounds
 };
-int policy_pass_incremental(nalar_policy* h, const nalar_problem* p, nalar_result* r, const IncStore& st);
+int policy_pass_incremental(nalar_policy* h, const nalar_problem* p, nalar_result* r, IncStore& st);
 // Full passes of the store leave splitters for any number of ready futures.
 void policy_split_any(nalar_policy* h, bool on);
 // Grows the handle's pass arena ahead of a pass over N futures of W
@@ -308,8 +327,15 @@ int policy_fail(nalar_policy* h, int code, const char* msg);
 // Validates the futures from v_begin on (and every deadline and instance).
 // done_bits (or null, and only with v_begin = 0): the done flags packed one
 // bit per future, bit v % 64 of word v / 64.
+// pack (or null): an incremental pass's flags made ready in the same launch.
+struct IncPack {
+  uint2* fl;                     // written: members = the futures from n_prev on, done flags packed
+  int64_t n_prev;
+  IncCtrl* ic;                   // cleared
+};
 hipError_t launch_nodes(hipStream_t s, const ProblemDev& p, Ctrl* ctrl, Ctrl* next_ctrl, ITab itab,
-                        int32_t* wf_off, int contiguous, int64_t v_begin = 0, uint64_t* done_bits = nullptr);
+                        int32_t* wf_off, int contiguous, int64_t v_begin = 0, uint64_t* done_bits = nullptr,
+                        const IncPack* pack = nullptr);
 
 // sort.hip (mark(ctx, name) is called before each launch, for timing)
 hipError_t launch_reset(hipStream_t s, Ctrl* c, uint32_t* clear, int64_t n_clear);

@@ -866,7 +866,7 @@ __device__ void bin_sort_one(const SortArgs& a, const BucketArgs& bk, int b, int
     if (j < J && i < n) {
       key[j] = rec[i].key;
       pos[j] = rec[i].pos;
-      if (tw) wfj[j] = tw[pos[j]];
+      if (tw) wfj[j] = a.tie_packed ? slot_wf(rec[i].route) : tw[pos[j]];
       kmin = key[j] < kmin ? key[j] : kmin;
       kmax = key[j] > kmax ? key[j] : kmax;
     }

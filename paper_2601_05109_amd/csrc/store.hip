@@ -44,14 +44,18 @@ struct nalar_store {
                                 //   stored futures must be validated again, in a full pass)
   int64_t capI = 0;             // futures the incremental buffers hold
   int64_t* rem = nullptr;       // [capI]
-  uint32_t* inA = nullptr;      // [capI / 32 + 1]
-  uint32_t* dnb = nullptr;      // [capI / 32 + 1] done flags as bits (pass scratch)
+  uint2* fl = nullptr;          // [capI / 32 + 1] membership and done bits (pass scratch)
   int64_t* mxA = nullptr;
   int32_t* cntA = nullptr;
   int32_t* light = nullptr;
   int32_t* heavy = nullptr;
-  int32_t* rlist = nullptr;
+  uint64_t* rbits = nullptr;    // [capI / 64 + 1]
+  int32_t* hv = nullptr;        // [capH] futures with more than kIncHeavy dependencies
+  int32_t* rheavy = nullptr;    // [capH]
+  uint32_t* hv_n = nullptr;     // their number (device memory; the appends count)
+  int64_t capH = 0;
   IncCtrl* ic = nullptr;
+  uint32_t rounds = kIncRoundsAll;  // depth of the last incremental pass (the next one's launch plan)
   int32_t* log = nullptr;       // ids completed since the last pass
   int64_t n_log = 0, capLog = 0;
 };
@@ -90,6 +94,10 @@ struct AppendArgs {
   int64_t n, n_edges;
   int32_t base;
   uint32_t* bad;
+  int32_t id0;                  // id of the first appended future
+  int32_t* hv;                  // futures with more than kIncHeavy dependencies
+  uint32_t* hv_n;
+  int64_t hv_cap;
 };
 
 __global__ __launch_bounds__(kStoreThreads) void k_store_append(AppendArgs a) {
@@ -105,6 +113,13 @@ __global__ __launch_bounds__(kStoreThreads) void k_store_append(AppendArgs a) {
     const int32_t x0 = a.soff[i], x1 = a.soff[i + 1];
     b |= x1 < x0 || (i == 0 && x0 != 0) || (i == a.n - 1 && int64_t(x1) != a.n_edges);
     a.off[i + 1] = a.base + x1;
+    // (the degree as stored: off[0] was written by the append before)
+    const int64_t deg = int64_t(a.base) + x1 - (i == 0 ? int64_t(a.off[0]) : int64_t(a.base) + x0);
+    if (deg > kIncHeavy) {
+      const uint32_t at = atomicAdd(a.hv_n, 1u);
+      if (int64_t(at) < a.hv_cap) a.hv[at] = a.id0 + int32_t(i);
+      else b = true;  // more than the edges allow: malformed offsets
+    }
   }
   for (int64_t e = g0; e < a.n_edges; e += step) a.idx[e] = a.sidx[e];
   if (ballot(b) != 0 && lane_id() == 0)
@@ -178,13 +193,12 @@ int ensure_incremental(nalar_store* st) {
   if (nc < need) nc = need;
   int64_t c;
   c = st->capI; e = grow(st->rem, c, nc, st->rem_valid ? st->n_prev : 0, s);
-  if (e == hipSuccess) { c = st->capI / 32 + 1; e = grow(st->inA, c, nc / 32 + 1, 0, s); }
-  if (e == hipSuccess) { c = st->capI / 32 + 1; e = grow(st->dnb, c, nc / 32 + 1, 0, s); }
+  if (e == hipSuccess) { c = st->capI / 32 + 1; e = grow(st->fl, c, nc / 32 + 1, 0, s); }
   if (e == hipSuccess) { c = st->capI; e = grow(st->mxA, c, nc, 0, s); }
-  if (e == hipSuccess) { c = st->capI; e = grow(st->cntA, c, nc, 0, s); }
+  if (e == hipSuccess) { c = st->capI; e = grow(st->cntA, c, nc + 32, 0, s); }  // whole words of 32
   if (e == hipSuccess) { c = st->capI; e = grow(st->light, c, nc, 0, s); }
   if (e == hipSuccess) { c = st->capI; e = grow(st->heavy, c, nc, 0, s); }
-  if (e == hipSuccess) { c = st->capI; e = grow(st->rlist, c, nc, 0, s); }
+  if (e == hipSuccess) { c = st->capI / 64 + 1; e = grow(st->rbits, c, nc / 64 + 1, 0, s); }
   if (e != hipSuccess) {
     st->rem_valid = false;
     return store_fail(st, e, "store incremental");
@@ -223,9 +237,10 @@ void nalar_store_destroy(nalar_store* st) {
                   static_cast<void*>(st->done), static_cast<void*>(st->loc), static_cast<void*>(st->dep_off),
                   static_cast<void*>(st->dep_idx), static_cast<void*>(st->deadline),
                   static_cast<void*>(st->inst_type), static_cast<void*>(st->inst_load),
-                  static_cast<void*>(st->inst_speed), static_cast<void*>(st->rem), static_cast<void*>(st->inA), static_cast<void*>(st->dnb),
+                  static_cast<void*>(st->inst_speed), static_cast<void*>(st->rem), static_cast<void*>(st->fl),
                   static_cast<void*>(st->mxA), static_cast<void*>(st->cntA), static_cast<void*>(st->light),
-                  static_cast<void*>(st->heavy), static_cast<void*>(st->rlist), static_cast<void*>(st->ic),
+                  static_cast<void*>(st->heavy), static_cast<void*>(st->rbits), static_cast<void*>(st->ic),
+                  static_cast<void*>(st->hv), static_cast<void*>(st->rheavy), static_cast<void*>(st->hv_n),
                   static_cast<void*>(st->log)})
     if (p) (void)hipFree(p);
   if (st->bad) (void)hipHostFree(st->bad);
@@ -271,10 +286,24 @@ int nalar_store_append(nalar_store* st, int64_t n_new, int64_t n_new_edges, cons
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return store_fail(st, e, "store init");
   }
+  {  // room for every future of more than kIncHeavy dependencies
+    const int64_t need_h = (E + n_new_edges) / (kIncHeavy + 1) + 1;
+    if (!st->hv_n) {
+      e = hipMalloc(&st->hv_n, sizeof(uint32_t));
+      if (e == hipSuccess) e = launch_inc_clear(s, st->hv_n, 1);
+      if (e != hipSuccess) return store_fail(st, e, "store grow");
+    }
+    if (need_h > st->capH) {
+      int64_t c0 = st->capH;
+      e = grow(st->rheavy, c0, need_h, 0, s);
+      if (e == hipSuccess) e = grow(st->hv, st->capH, need_h, st->capH, s);
+      if (e != hipSuccess) return store_fail(st, e, "store grow");
+    }
+  }
   if (n_new > 0) {
     const AppendArgs aa{st->wf + N, st->type + N, st->est + N, st->done + N, st->loc + N, st->dep_off + N,
                         st->dep_idx + E, wf, type, est_us, done, loc, dep_off, dep_idx, n_new, n_new_edges,
-                        int32_t(E), st->bad};
+                        int32_t(E), st->bad, int32_t(N), st->hv, st->hv_n, st->capH};
     hipLaunchKernelGGL(k_store_append, dim3(grid_for(n_new > n_new_edges ? n_new : n_new_edges)),
                        dim3(kStoreThreads), 0, s, aa);
     e = hipGetLastError();
@@ -391,9 +420,11 @@ int nalar_store_pass(nalar_store* st, int64_t now_us, int64_t migration_cost_us,
   else if (!st->rem_valid || !r) st->last_fallback = NALAR_STORE_FULL_NO_STATE;
   else if (st->W < st->W_prev || st->M < st->M_prev) st->last_fallback = NALAR_STORE_FULL_SHRUNK;
   else {
-    const IncStore is{st->n_prev, st->log, st->n_log, st->rem, st->inA, st->dnb, st->mxA, st->cntA,
-                      st->light, st->heavy, st->rlist, st->ic};
+    IncStore is{st->n_prev, st->log, st->n_log, st->rem, st->fl, st->mxA, st->cntA, st->light,
+                      st->heavy, st->rbits, st->hv, st->hv_n, st->capH, st->rheavy, st->ic,
+                st->rounds};
     rc = policy_pass_incremental(st->h, &p, r, is);
+    st->rounds = is.rounds;
     if (!inc_fallback(rc)) st->last_incremental = 1;
     st->last_fallback = rc == kIncFallback ? NALAR_STORE_FULL_NO_SPLITTERS
                       : rc == kIncFallbackOverflow ? NALAR_STORE_FULL_OVERFLOW

@@ -13,7 +13,9 @@ if not torch.cuda.is_available():  # pragma: no cover - collected on CPU hosts t
     pytest.skip("no GPU", allow_module_level=True)
 
 from paper_2601_05109_amd import nalar  # noqa: E402
-from test_gpu_parity import _one_type, check, policy  # noqa: E402,F401
+import oracle  # noqa: E402
+from test_gpu_parity import _one_type, assert_parity, check, policy, say  # noqa: E402,F401
+from test_gpu_store_incremental import feed, store_pass  # noqa: E402
 
 
 # ---------------------------------------------------------------- greedy routing
@@ -75,3 +77,64 @@ def test_weighted_tiles(policy, n, m, n_types):  # noqa: F811
         check(policy, p, f"weighted n={n} pass {rep}", policy=W, weights=w)
     check(policy, p, f"weighted stateful n={n}", policy=W | nalar.NALAR_ROUTE_STATEFUL | nalar.NALAR_ORDER_LPT,
           weights=w)
+
+
+# ---------------------------------------------------------------- incremental store passes
+
+def _fan_in_store(n, W, seed):
+    """Workflow 0: up to 300 futures, the last depending on all others (more than
+    64: expanded by a workgroup); then one-future workflows with few distinct
+    keys, so that ties are broken by (workflow, id)."""
+    rng = np.random.default_rng(seed)
+    k = min(n, 300)
+    wf = np.zeros(n, np.int32)
+    wf[k:] = rng.integers(0, W, n - k)
+    counts = np.zeros(n, np.int64)
+    counts[k - 1] = k - 1
+    dep_off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    dep_idx = np.arange(k - 1, dtype=np.int32)
+    now, M, K = 10_000, 12, 3
+    return wl.Problem(f"fan-in-{n}", now, 150_000, wf, rng.integers(0, K, n).astype(np.int32),
+                      rng.integers(1, 4 + n // 300, n).astype(np.int64) * 100, np.zeros(n, np.uint8),
+                      np.where(rng.random(n) < 0.5, rng.integers(0, M, n), -1).astype(np.int32), dep_off, dep_idx,
+                      (now + rng.integers(1, 4 + n // 300, W) * 1000).astype(np.int64), (np.arange(M) % K).astype(np.int32),
+                      rng.integers(0, 10**6, M).astype(np.int64), rng.integers(300, 3000, M).astype(np.int32),
+                      wf_contiguous=False)
+
+
+def _extended(p, done_ids, parents, seed):
+    """p with the ids done and one child appended per parent."""
+    rng = np.random.default_rng(seed)
+    t = len(parents)
+    done = p.done.copy()
+    done[done_ids] = 1
+    cat = lambda a, b: np.concatenate([a, np.asarray(b, a.dtype)])  # noqa: E731
+    return wl.Problem(p.name, p.now_us, p.migration_cost_us, cat(p.wf, p.wf[parents]),
+                      cat(p.type, rng.integers(0, 3, t)), cat(p.est_us, rng.integers(1, 500, t)), cat(done, np.zeros(t)),
+                      cat(p.loc, np.full(t, -1)), cat(p.dep_off, p.dep_off[-1] + np.arange(1, t + 1)),
+                      cat(p.dep_idx, parents), p.deadline_us, p.inst_type, p.inst_load_us, p.inst_speed_permille,
+                      wf_contiguous=False)
+
+
+@pytest.mark.parametrize("W", [3, 65_536, 65_537])
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 65, 66, 255, 257, 2049, 4097, 70_001])
+def test_store_incremental_sizes(n, W):
+    """Incremental passes around the sizes their kernels work in (words of 32 and
+    64 futures, units of 256, steps of 2,048 and 4,096), and around 65,536
+    workflows, up to which the records carry the workflow of a tie."""
+    p = _fan_in_store(n, W, n + W)
+    with nalar.Policy() as pol, nalar.Store(pol) as st:
+        prev = feed(st, p, 0, None)
+        g, _ = store_pass(pol, st, p)
+        assert_parity(g, oracle.run(p), "full")
+        rng = np.random.default_rng(n)
+        for tick in range(3):
+            every = np.arange(min(n, 300) - 1, dtype=np.int64)
+            ids = every[tick::2] if tick < 2 else rng.choice(p.n_nodes, min(p.n_nodes, 40), replace=False)
+            p = _extended(p, ids, rng.integers(0, p.n_nodes, 1 + tick * 40), tick)
+            prev = feed(st, p, *prev)
+            g, inc = store_pass(pol, st, p, policy=(0, nalar.NALAR_ORDER_LPT, nalar.NALAR_ORDER_SRTF)[tick])
+            assert_parity(g, oracle.run(p, policy=(0, nalar.NALAR_ORDER_LPT, nalar.NALAR_ORDER_SRTF)[tick]),
+                          f"n={n} W={W} tick {tick}")
+            say(f"n={n} W={W} tick {tick}: incremental {inc}, reason {st.last_fallback}")
+            assert inc or tick > 0  # (another order's keys may overflow bins cut for this one)
