@@ -138,3 +138,50 @@ def test_store_incremental_sizes(n, W):
                           f"n={n} W={W} tick {tick}")
             say(f"n={n} W={W} tick {tick}: incremental {inc}, reason {st.last_fallback}")
             assert inc or tick > 0  # (another order's keys may overflow bins cut for this one)
+
+
+# ---------------------------------------------------------------- wave sweep
+
+def _chained(W, n, seed, heavy):
+    """W contiguous workflows of n futures, each on the one before it in a window
+    of 70 (mostly the last one: as deep as it is long) and up to two more."""
+    rng = np.random.default_rng(seed)
+    counts, flat = [], []
+    for w in range(W):
+        for i in range(n):
+            par = set()
+            if i:
+                par.add(i - 1 if rng.random() < 0.8 else int(rng.integers(max(0, i - 70), i)))
+                for _ in range(int(rng.integers(0, 3))):
+                    par.add(int(rng.integers(max(0, i - 70), i)))
+                if heavy and i % 17 == 16:
+                    par |= set(int(x) for x in rng.integers(0, i, 6))
+            counts.append(len(par))
+            flat += [w * n + q for q in sorted(par)]
+    N, M, K, now = W * n, 9, 3, 5_000
+    return wl.Problem(f"chained-{W}x{n}", now, 150_000, np.repeat(np.arange(W, dtype=np.int32), n),
+                      rng.integers(0, K, N).astype(np.int32), rng.integers(0, 10**5, N).astype(np.int64),
+                      (np.tile(np.arange(n), W) < 3 * n // 10).astype(np.uint8),
+                      np.where(rng.random(N) < 0.5, rng.integers(0, M, N), -1).astype(np.int32),
+                      np.concatenate([[0], np.cumsum(counts)]).astype(np.int32), np.asarray(flat, np.int32),
+                      (now + rng.integers(0, 10**7, W)).astype(np.int64), (np.arange(M) % K).astype(np.int32),
+                      rng.integers(0, 10**6, M).astype(np.int64), rng.integers(300, 3000, M).astype(np.int32),
+                      wf_contiguous=True)
+
+
+@pytest.mark.parametrize("heavy", [False, True])
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 63, 64, 65, 128, 129, 255, 257, 512])
+def test_wave_sweep_orders(policy, n, heavy):  # noqa: F811
+    """One wave per workflow (or pair) around its groups of 64 positions, with
+    ids in topological order (no counters), reversed and shuffled inside each
+    workflow, and with one workflow of several out of order."""
+    W = 11
+    p = _chained(W, n, n, heavy)
+    local = np.tile(np.arange(n), W)
+    base = np.repeat(np.arange(W) * n, n)
+    rng = np.random.default_rng(n)
+    shuffled = np.concatenate([w * n + rng.permutation(n) for w in range(W)])
+    one = np.concatenate([w * n + (rng.permutation(n) if w == 3 else np.arange(n)) for w in range(W)])
+    for name, perm in (("topological", np.arange(W * n)), ("reversed", base + n - 1 - local),
+                       ("shuffled", shuffled), ("one-shuffled", one)):
+        check(policy, wl.relabel(p, perm), f"{name} n={n} heavy={heavy}")
