@@ -719,9 +719,10 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
     g.pos_of_node = A.pos_of_node;
     g.wf_off = A.wf_off;
     g.cap_n = A.capN > 0 ? A.capN : 1;
+    g.mat = reinterpret_cast<uint32_t*>(A.skey[0]);  // the slack sort's keys come later
     e = launch_group(s, g, Timer::cb, &tm);
     if (e != hipSuccess) return hip_fail(h, e, "group");
-    node_of_pos = reinterpret_cast<const int32_t*>(A.gpay[(g.npass - 1) & 1]);
+    node_of_pos = reinterpret_cast<const int32_t*>(A.gpay[group_places_first(g) ? 0 : (g.npass - 1) & 1]);
     pos_of_node = A.pos_of_node;
   }
 

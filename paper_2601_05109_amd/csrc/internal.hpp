@@ -78,6 +78,7 @@ struct GroupArgs {
   int32_t* pos_of_node;
   int32_t* wf_off;
   int64_t cap_n;                // entries each key and payload buffer holds
+  uint32_t* mat;                // [2 * cap_n] tile counts of the grouping by many workflows
 };
 
 // Buckets of the bucketed slack sort (nb == 0: not used this pass).  Bucket of
@@ -347,6 +348,8 @@ hipError_t prepare_sort_kernels();  // LDS limits of the sort kernels (at handle
 hipError_t launch_splitters(hipStream_t s, const SortArgs& a);
 hipError_t launch_slack_sort(hipStream_t s, const SortArgs& a, int first_pass, int last_pass,
                              void (*mark)(void*, const char*), void* ctx);
+// The grouped ids end in pay[0] whatever npass (else in pay[(npass - 1) & 1]).
+bool group_places_first(const GroupArgs& a);
 hipError_t launch_group(hipStream_t s, const GroupArgs& a, void (*mark)(void*, const char*),
                         void* ctx);
 

@@ -1280,6 +1280,206 @@ __global__ __launch_bounds__(kSortThreads) void k_group1_place(GroupArgs a) {
   }
 }
 
+// Grouping by workflow for more than kRadixBuckets workflows, up to
+// kGroupWMax, in three launches like the ones above: a tile's counts are one
+// LDS word per workflow, its row of the count matrix holds one word per
+// workflow, and the scan runs down the matrix's columns.  The tile grows with
+// the workflows (at least half as many ids), so the matrix stays below two words
+// per id.  Inside a tile the stable rank comes from ballots over the workflow's
+// bits, per row of 64 ids and wave in parallel; only the addition of a row's
+// counts to the running ones is in order (waves in turn).
+//
+// Bound by latency at the sizes this serves: 131,072 ids in creation order over
+// 4,096 workflows took 48 us as a histogram, two look-back digit passes and a
+// finishing kernel; the whole pass over 131,072 such futures went from 93 to
+// 64 us.
+constexpr int kGroupWThreads = 256;
+constexpr int kGroupWWaves = kGroupWThreads / kWave;
+constexpr int kGroupWRows = 4;                                      // rows of 64 ids per wave and sub-tile
+constexpr int kGroupWSub = kGroupWThreads * kGroupWRows;            // ids per sub-tile
+constexpr int64_t kGroupWMax = 16384;                               // LDS: 64 KB of counts
+constexpr int kGroupWCols = 64, kGroupWSegs = 16, kGroupWPer = 8;   // column scan: 16 segments of 8 tiles
+
+// Ids per tile, or 0 when this grouping does not apply.
+int64_t groupw_tile(int64_t N, int64_t W, int64_t cap_n) {
+  if (W <= kRadixBuckets || W > kGroupWMax || W > cap_n) return 0;
+  int64_t tile = kGroupWSub;
+  while (tile * 2 < W) tile *= 2;
+  const int64_t tiles = (N + tile - 1) / tile;
+  return tiles * W <= 2 * cap_n ? tile : 0;
+}
+
+__global__ __launch_bounds__(kGroupWThreads) void k_groupw_count(GroupArgs a, int tile_ids) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  uint32_t* H = reinterpret_cast<uint32_t*>(smem);
+  if (a.ctrl->status) return;
+  const int64_t N = a.p.N;
+  const int W = int(a.p.W);
+  const int64_t t0 = int64_t(blockIdx.x) * tile_ids;
+  for (int w = threadIdx.x; w < W; w += kGroupWThreads) H[w] = 0;
+  __syncthreads();
+  for (int s0 = 0; s0 < tile_ids; s0 += kGroupWSub) {
+    int32_t d[kGroupWRows];
+#pragma unroll
+    for (int r = 0; r < kGroupWRows; ++r) {
+      const int64_t i = t0 + s0 + r * kGroupWThreads + threadIdx.x;
+      d[r] = i < N ? a.p.wf[i] : -1;
+    }
+#pragma unroll
+    for (int r = 0; r < kGroupWRows; ++r)
+      if (d[r] >= 0) atomicAdd(&H[d[r]], 1u);
+  }
+  __syncthreads();
+  uint32_t* row = a.mat + int64_t(blockIdx.x) * W;
+  for (int w = threadIdx.x; w < W; w += kGroupWThreads) row[w] = H[w];
+}
+
+// Columns of the matrix: each count becomes the workflow's futures in earlier
+// tiles; a.key[1] receives the workflows' totals.  Thread (segment, column).
+// (Scanning the totals here too, by look-back over the workgroups, took as much
+// more here as it saved in every placing tile.)
+__global__ __launch_bounds__(kGroupWCols* kGroupWSegs) void k_groupw_scan(GroupArgs a, int64_t tiles) {
+  __shared__ uint32_t s_sum[kGroupWSegs][kGroupWCols];
+  if (a.ctrl->status) return;
+  const int W = int(a.p.W);
+  const int col = threadIdx.x % kGroupWCols, seg = threadIdx.x / kGroupWCols;
+  const int w = blockIdx.x * kGroupWCols + col;
+  uint32_t carry = 0;
+  for (int64_t t0 = 0; t0 < tiles; t0 += kGroupWSegs * kGroupWPer) {
+    uint32_t c[kGroupWPer], sum = 0;
+#pragma unroll
+    for (int u = 0; u < kGroupWPer; ++u) {
+      const int64_t t = t0 + seg * kGroupWPer + u;
+      c[u] = t < tiles && w < W ? a.mat[t * W + w] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < kGroupWPer; ++u) sum += c[u];
+    s_sum[seg][col] = sum;
+    __syncthreads();
+    uint32_t run = carry;
+#pragma unroll
+    for (int q = 0; q < kGroupWSegs; ++q) {
+      const uint32_t x = s_sum[q][col];
+      run += q < seg ? x : 0u;
+      carry += x;
+    }
+#pragma unroll
+    for (int u = 0; u < kGroupWPer; ++u) {
+      const int64_t t = t0 + seg * kGroupWPer + u;
+      if (t < tiles && w < W) a.mat[t * W + w] = run;
+      run += c[u];
+    }
+    __syncthreads();
+  }
+  if (seg == 0 && w < W) a.key[1][w] = carry;
+}
+
+__global__ __launch_bounds__(kGroupWThreads) void k_groupw_place(GroupArgs a, int tile_ids, int bits) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  uint32_t* run = reinterpret_cast<uint32_t*>(smem);  // [W, whole uint4s] next position of the workflow's futures
+  __shared__ uint32_t s_tmp[kGroupWWaves];
+  if (a.ctrl->status) return;
+  const int64_t N = a.p.N;
+  const int W = int(a.p.W);
+  const int tid = threadIdx.x, wv = tid / kWave, ln = lane_id();
+  const int64_t tile = blockIdx.x;
+  {  // the workflows' first positions (a scan of the totals, 16 consecutive ones
+     // per thread), then, coalesced, this tile's; every load of a step in flight
+    constexpr int V = 16;
+    uint32_t carry = 0;
+    for (int w0 = 0; w0 < W; w0 += kGroupWThreads * V) {
+      const int wt = w0 + tid * V;
+      uint4 t4[V / 4];
+      uint32_t m[V], sum = 0;
+#pragma unroll
+      for (int u = 0; u < V / 4; ++u)  // (a word past the last workflow is dropped below)
+        t4[u] = wt + 4 * u < W ? *reinterpret_cast<const uint4*>(a.key[1] + wt + 4 * u) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < V; ++u) {
+        const int w = w0 + u * kGroupWThreads + tid;
+        m[u] = w < W ? a.mat[tile * W + w] : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < V / 4; ++u) {
+        const int w = wt + 4 * u;
+        if (w + 1 >= W) t4[u].y = 0;
+        if (w + 2 >= W) t4[u].z = 0;
+        if (w + 3 >= W) t4[u].w = 0;
+        sum += t4[u].x + t4[u].y + t4[u].z + t4[u].w;
+      }
+      const uint32_t inc = wave_incl_scan_u32(sum);
+      if (ln == kWave - 1) s_tmp[wv] = inc;
+      __syncthreads();
+      uint32_t at = carry + inc - sum;
+#pragma unroll
+      for (int q = 0; q < kGroupWWaves; ++q) {
+        at += q < wv ? s_tmp[q] : 0u;
+        carry += s_tmp[q];
+      }
+#pragma unroll
+      for (int u = 0; u < V / 4; ++u) {
+        uint4 x;
+        x.x = at;
+        x.y = x.x + t4[u].x;
+        x.z = x.y + t4[u].y;
+        x.w = x.z + t4[u].z;
+        at = x.w + t4[u].w;
+        if (wt + 4 * u < W) *reinterpret_cast<uint4*>(run + wt + 4 * u) = x;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < V; ++u) {
+        const int w = w0 + u * kGroupWThreads + tid;
+        if (w >= W) continue;
+        const uint32_t start = run[w];
+        if (tile == 0) a.wf_off[w] = int32_t(start);
+        run[w] = start + m[u];
+      }
+    }
+    if (tile == 0 && tid == 0) a.wf_off[W] = int32_t(N);
+  }
+  __syncthreads();
+  for (int s0 = 0; s0 < tile_ids; s0 += kGroupWSub) {
+    // wave w: ids base + w * 256 + row * 64 + lane
+    const int64_t base = tile * tile_ids + s0 + wv * (kWave * kGroupWRows) + ln;
+    int32_t d[kGroupWRows];
+    uint32_t below[kGroupWRows], all[kGroupWRows], q[kGroupWRows];
+#pragma unroll
+    for (int r = 0; r < kGroupWRows; ++r) d[r] = base + r * kWave < N ? a.p.wf[base + r * kWave] : -1;
+#pragma unroll
+    for (int r = 0; r < kGroupWRows; ++r) {
+      uint64_t m = ballot(d[r] >= 0);  // the row's lanes holding the same workflow
+      for (int b = 0; b < bits; ++b) {
+        const bool on = (uint32_t(d[r]) >> b) & 1u;
+        const uint64_t x = ballot(on);
+        m &= on ? x : ~x;
+      }
+      below[r] = lanes_below(m);
+      all[r] = uint32_t(__popcll(m));
+      q[r] = 0;
+    }
+    for (int turn = 0; turn < kGroupWWaves; ++turn) {
+      if (wv == turn) {
+#pragma unroll
+        for (int r = 0; r < kGroupWRows; ++r) {
+          if (d[r] >= 0) q[r] = run[d[r]];
+          __asm__ __volatile__("" ::: "memory");  // one wave's LDS accesses complete in order
+          if (d[r] >= 0 && below[r] == 0) run[d[r]] = q[r] + all[r];
+          __asm__ __volatile__("" ::: "memory");
+        }
+      }
+      lds_barrier();
+    }
+#pragma unroll
+    for (int r = 0; r < kGroupWRows; ++r) {
+      if (d[r] < 0) continue;
+      const uint32_t at = q[r] + below[r];
+      a.pay[0][at] = uint32_t(base + r * kWave);
+      a.pos_of_node[base + r * kWave] = int32_t(at);
+    }
+  }
+}
+
 __global__ __launch_bounds__(kSortThreads) void k_group_hist(GroupArgs a) {
   __shared__ uint32_t H[kMaxSortPasses][kRadixBuckets];
   if (a.ctrl->status) return;
@@ -1365,6 +1565,10 @@ hipError_t launch_bin_sort(hipStream_t s, const SortArgs& a, const BucketArgs& b
 }
 
 hipError_t prepare_sort_kernels() {
+  for (const void* k : {reinterpret_cast<const void*>(&k_groupw_count), reinterpret_cast<const void*>(&k_groupw_place)}) {
+    const hipError_t eg = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, int(4 * kGroupWMax));
+    if (eg != hipSuccess) return eg;
+  }
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bin_sort),
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
                                      int(bin_lds_bytes<kBinThreads / kWave>(kBinCap, true)));
@@ -1402,6 +1606,10 @@ hipError_t launch_slack_sort(hipStream_t s, const SortArgs& a, int first_pass, i
   return hipSuccess;
 }
 
+bool group_places_first(const GroupArgs& a) {
+  return a.npass == 1 || groupw_tile(a.p.N, a.p.W, a.cap_n) != 0;
+}
+
 hipError_t launch_group(hipStream_t s, const GroupArgs& a, void (*mark)(void*, const char*),
                         void* ctx) {
   const int64_t ntiles = (a.p.N + kSortTile - 1) / kSortTile;
@@ -1416,6 +1624,24 @@ hipError_t launch_group(hipStream_t s, const GroupArgs& a, void (*mark)(void*, c
     if (e != hipSuccess) return e;
     mark(ctx, "group_place");
     hipLaunchKernelGGL(k_group1_place, dim3(ntiles), dim3(kSortThreads), 0, s, a);
+    return hipGetLastError();
+  }
+  if (const int64_t tile = groupw_tile(a.p.N, a.p.W, a.cap_n)) {
+    const int64_t tiles = (a.p.N + tile - 1) / tile;
+    const size_t lds = 4 * size_t((a.p.W + 3) & ~int64_t(3));
+    int bits = 0;
+    while ((int64_t(1) << bits) < a.p.W) ++bits;
+    mark(ctx, "group_count");
+    hipLaunchKernelGGL(k_groupw_count, dim3(unsigned(tiles)), dim3(kGroupWThreads), lds, s, a, int(tile));
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    mark(ctx, "group_scan");
+    hipLaunchKernelGGL(k_groupw_scan, dim3(unsigned((a.p.W + kGroupWCols - 1) / kGroupWCols)),
+                       dim3(kGroupWCols * kGroupWSegs), 0, s, a, tiles);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    mark(ctx, "group_place");
+    hipLaunchKernelGGL(k_groupw_place, dim3(unsigned(tiles)), dim3(kGroupWThreads), lds, s, a, int(tile), bits);
     return hipGetLastError();
   }
   mark(ctx, "group_hist");

@@ -185,3 +185,28 @@ def test_wave_sweep_orders(policy, n, heavy):  # noqa: F811
     for name, perm in (("topological", np.arange(W * n)), ("reversed", base + n - 1 - local),
                        ("shuffled", shuffled), ("one-shuffled", one)):
         check(policy, wl.relabel(p, perm), f"{name} n={n} heavy={heavy}")
+
+
+# ---------------------------------------------------------------- grouping by workflow
+
+@pytest.mark.parametrize("W,n", [(256, 9), (257, 9), (1023, 3), (1024, 5), (2048, 1), (2049, 2), (4097, 3),
+                                 (16_384, 2), (16_385, 2), (300, 700)])
+def test_grouping_by_many_workflows(policy, W, n):  # noqa: F811
+    """Ids of W workflows in random order, around the counts at which the
+    grouping changes (256 and 16,384 workflows) and its tile grows (2,048, 4,096
+    ...), with workflows left empty and one larger than the others."""
+    rng = np.random.default_rng(W + n)
+    p = _chained(W, n, W, False)
+    keep = np.flatnonzero((p.wf % 7 != 3) | (p.wf == W - 1))  # some workflows without futures
+    new = np.full(p.n_nodes, -1)
+    new[keep] = np.arange(keep.size)
+    cnt = np.diff(p.dep_off)[keep]
+    idx = np.concatenate([p.dep_idx[p.dep_off[v]:p.dep_off[v + 1]] for v in keep]) if cnt.sum() else p.dep_idx[:0]
+    q = wl.Problem(p.name, p.now_us, p.migration_cost_us, *[np.ascontiguousarray(getattr(p, f)[keep])
+                                                            for f in wl.Problem.NODE_FIELDS],
+                   np.concatenate([[0], np.cumsum(cnt)]).astype(np.int32), new[idx].astype(np.int32), p.deadline_us,
+                   p.inst_type, p.inst_load_us, p.inst_speed_permille)
+    perm = rng.permutation(q.n_nodes)
+    r = wl.relabel(q, perm)
+    for rep in range(2):
+        check(policy, r, f"grouped W={W} n={n} pass {rep}", flags=0)
