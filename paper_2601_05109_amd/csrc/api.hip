@@ -1023,6 +1023,7 @@ int nalar::policy_pass_incremental(nalar_policy* h, const nalar_problem* p, nala
   ia.cntA = st.cntA;
   ia.light = st.light;
   ia.heavy = st.heavy;
+  ia.att = st.att;
   ia.rbits = st.rbits;
   ia.hv = st.hv;
   ia.hv_n = st.hv_n;

@@ -511,18 +511,7 @@ __global__ __launch_bounds__(kIncThreads) void k_inc_scan(IncArgs a, int hb) {
         bool blocked = false;
         int64_t rv = 0;
         bool have_rv = false;
-        for (int32_t e = o0[j]; e < o1[j]; ++e) {
-          int32_t d;
-          uint2 w;
-          if (e == o0[j]) {  // the first dependency, loaded above
-            d = d0[j];
-            w = df[j];
-          } else {
-            d = a.p.dep_idx[e];
-            if (int64_t(d) >= N) d = -1;
-            w = a.fl[d >= 0 ? uint32_t(d) >> 5 : 0u];
-          }
-          if (d < 0) continue;  // reported by the closure or an earlier pass
+        auto visit = [&](int32_t d, const uint2& w) {
           blocked |= !bit_of(w.y, d);
           if (in) {
             if (d != pc.d) {
@@ -543,6 +532,15 @@ __global__ __launch_bounds__(kIncThreads) void k_inc_scan(IncArgs a, int hb) {
             }
             pm.v = rv > pm.v ? rv : pm.v;
           }
+        };
+        // (out of range: reported by the closure or an earlier pass.  The first
+        // dependency, loaded above, has a visit of its own: choosing between it
+        // and the loaded one inside the loop made the compiler keep the loaded
+        // ones in scratch memory and read either through one pointer.)
+        if (d0[j] >= 0) visit(d0[j], df[j]);
+        for (int32_t e = o0[j] + 1; e < o1[j]; ++e) {
+          const int32_t d = a.p.dep_idx[e];
+          if (d >= 0 && int64_t(d) < N) visit(d, a.fl[uint32_t(d) >> 5]);
         }
         ready = !bit_of(f[j].y, int32_t(v)) && !blocked;
       }
@@ -552,9 +550,11 @@ __global__ __launch_bounds__(kIncThreads) void k_inc_scan(IncArgs a, int hb) {
     // the wave's word of item j covers futures g0 + j * kIncThreads + 64 wv ..
     const int64_t rw = (g0 + int64_t(ln) * kIncThreads + int64_t(wv) * kWave) / kWave;
     if (ln < kScanPer && rw * kWave < N) a.rbits[rw] = rword;
+    // pushes still pending go out per wave, before the next tile's would push
+    // them out lane by lane (a hub's children: 64 atomics queueing on one word)
+    flush_wave_cnt(a.cntA, pc);
+    flush_wave_max(a.mxA, pm);
   }
-  flush_wave_cnt(a.cntA, pc);
-  flush_wave_max(a.mxA, pm);
   const uint32_t mt = uint32_t(wave_sum_i64(int64_t(members)));
   if (ln == 0) s_members[wv] = mt;
   __syncthreads();
@@ -805,8 +805,9 @@ __device__ inline int64_t key_of(uint32_t policy, int64_t rem, int64_t dl) {
 // memory side, about 12 per ns on the whole chip) and the sparse gathers bound
 // it, so a workgroup is as large as it can be, and a chunk as long: half the
 // segments of 1,024-future chunks over 256-thread workgroups.  At 12.4M futures,
-// 2.3M ready, 159 us and a 40 us copy of rem became 155 us; at 1.3M 42 + 5
-// became 34.
+// 2.3M ready, 159 us and a 40 us copy of rem became 155 us, and 134 us with the
+// attributes gathered as one record per future instead of four arrays; at 1.3M
+// 42 + 5 became 34 (512 threads, in chunks of 4,096 or 8,192: 42 to 47).
 constexpr int kReadyThreads = 1024;
 constexpr int kReadyPer = 8;                          // ready futures per thread and chunk
 constexpr int kReadyChunk = kReadyPer * kReadyThreads;
@@ -860,7 +861,8 @@ __device__ inline void ready_chunk(const IncArgs& a, const ReadyLds& S, int firs
   const uint32_t policy = a.p.policy;
   const bool out_slack = (policy & (NALAR_ORDER_LPT | NALAR_ORDER_SRTF)) != 0;
   const bool pack_wf = a.p.W <= kPackWf;
-  int32_t v[kReadyPer], wf[kReadyPer];
+  int32_t v[kReadyPer];
+  uint4 at[kReadyPer];
   int64_t key[kReadyPer];
   uint32_t bin[kReadyPer];  // bin, then bin | rank << 16 (rank < kReadyChunk)
   static_assert(kBinMax <= 65536 && kReadyChunk <= 65536, "bin and rank share a word");
@@ -868,14 +870,14 @@ __device__ inline void ready_chunk(const IncArgs& a, const ReadyLds& S, int firs
   for (int j = 0; j < kReadyPer; ++j) v[j] = j * T + tid < n ? S.list[first + j * T + tid] : -1;
 #pragma unroll
   for (int j = 0; j < kReadyPer; ++j) {
-    wf[j] = v[j] >= 0 ? a.p.wf[v[j]] : 0;
-    key[j] = v[j] >= 0 ? a.rem[v[j]] : 0;
+    at[j] = a.att[v[j] >= 0 ? v[j] : 0];
+    key[j] = a.rem[v[j] >= 0 ? v[j] : 0];
   }
 #pragma unroll
   for (int j = 0; j < kReadyPer; ++j) {
     bin[j] = 0;
     if (v[j] < 0) continue;
-    const int64_t dl = a.p.deadline[wf[j]] - a.p.now;
+    const int64_t dl = a.p.deadline[at[j].y] - a.p.now;
     if (out_slack) a.stg_oslack[v[j]] = dl - key[j];
     key[j] = key_of(policy, key[j], dl);
   }
@@ -908,27 +910,18 @@ __device__ inline void ready_chunk(const IncArgs& a, const ReadyLds& S, int firs
     }
   }
   __syncthreads();
-  int32_t ty[kReadyPer], lc[kReadyPer];
-  int64_t es[kReadyPer];
-#pragma unroll
-  for (int j = 0; j < kReadyPer; ++j) {
-    const int32_t u = v[j] >= 0 ? v[j] : 0;
-    ty[j] = a.p.type[u];
-    lc[j] = a.p.loc[u];
-    es[j] = a.p.est[u];
-  }
 #pragma unroll
   for (int j = 0; j < kReadyPer; ++j) {
     if (v[j] < 0) continue;
     int32_t route;
     int64_t cost;
-    route_future(ty[j], es[j], lc[j], int32_t(a.p.M), a.p.mig, S.type, S.idx, S.load, S.speed, S.inv, S.pos,
-                 S.run, (policy & NALAR_ROUTE_STATEFUL) != 0, route, cost, S.prun);
+    route_future(int32_t(at[j].x), att_est(at[j]), att_loc(at[j]), int32_t(a.p.M), a.p.mig, S.type, S.idx, S.load,
+                 S.speed, S.inv, S.pos, S.run, (policy & NALAR_ROUTE_STATEFUL) != 0, route, cost, S.prun);
     const uint32_t b = bin[j] & 0xFFFFu;
     const uint32_t slot = (bin[j] >> 16) + S.base[b];
     if (slot < uint32_t(a.bk.cap)) {
       int64_t* sl = reinterpret_cast<int64_t*>(a.bk.slot + int64_t(b) * a.bk.cap + slot);
-      const int32_t rw = pack_wf ? slot_pack_wf(route, wf[j]) : slot_pack(route, 0);
+      const int32_t rw = pack_wf ? slot_pack_wf(route, int32_t(at[j].y)) : slot_pack(route, 0);
       sl[0] = key[j];
       sl[1] = cost;
       sl[2] = int64_t(uint64_t(uint32_t(v[j])) | (uint64_t(uint32_t(rw)) << 32));

@@ -246,6 +246,22 @@ struct IncCtrl {
   uint32_t sh[kIncRounds + 1];   // sweep: futures pushed by a workgroup
 };
 
+// What routing and keying a future needs besides rem, in one 16-byte record
+// (they never change once appended): the ready futures lie sparsely among the
+// ids, so each array they are gathered from costs nearly all of its lines.  A
+// value out of range does not survive the packing, but then the pass fails.
+__host__ __device__ inline uint4 att_pack(int32_t wf, int32_t type, int64_t est, int32_t loc) {
+  uint4 a;
+  a.x = uint32_t(type);
+  a.y = uint32_t(wf);
+  a.z = uint32_t(uint64_t(est));
+  a.w = (uint32_t(uint64_t(est) >> 32) & 0xFFFFu) | (uint32_t(loc + 1) << 16);
+  return a;
+}
+__host__ __device__ inline int64_t att_est(const uint4& a) { return int64_t((uint64_t(a.w & 0xFFFFu) << 32) | a.z); }
+__host__ __device__ inline int32_t att_loc(const uint4& a) { return int32_t(a.w >> 16) - 1; }
+static_assert(NALAR_EST_MAX < (INT64_C(1) << 48) && NALAR_MAX_INSTANCES < 65536, "fields of att_pack");
+
 struct IncArgs {
   ProblemDev p;                  // the store's snapshot
   int64_t n_prev;                // futures rem covers from the last pass
@@ -259,6 +275,7 @@ struct IncArgs {
   int32_t* cntA;                 // [N] closure consumers not yet finalised (members)
   int32_t* light;                // [N] per-round lists
   int32_t* heavy;                // [N]
+  const uint4* att;              // [N] att_pack of each future
   uint64_t* rbits;               // [ceil(N/64)] ready futures with few dependencies, as bits
   const int32_t* hv;             // [hv_cap] futures with more than kIncHeavy dependencies
   const uint32_t* hv_n;          //   and their number
@@ -303,6 +320,7 @@ struct IncStore {
   int32_t* cntA;
   int32_t* light;
   int32_t* heavy;
+  const uint4* att;
   uint64_t* rbits;
   const int32_t* hv;
   const uint32_t* hv_n;

@@ -25,6 +25,7 @@ struct nalar_store {
   int64_t* est = nullptr;
   uint8_t* done = nullptr;
   int32_t* loc = nullptr;
+  uint4* att = nullptr;         // [capN] att_pack, for the incremental passes
   int32_t* dep_off = nullptr;   // [capN + 1]
   int32_t* dep_idx = nullptr;   // [capE]
   int64_t* deadline = nullptr;  // [capW]
@@ -94,6 +95,7 @@ struct AppendArgs {
   int64_t n, n_edges;
   int32_t base;
   uint32_t* bad;
+  uint4* att;
   int32_t id0;                  // id of the first appended future
   int32_t* hv;                  // futures with more than kIncHeavy dependencies
   uint32_t* hv_n;
@@ -105,11 +107,14 @@ __global__ __launch_bounds__(kStoreThreads) void k_store_append(AppendArgs a) {
   const int64_t step = int64_t(gridDim.x) * kStoreThreads;
   const int64_t g0 = int64_t(blockIdx.x) * kStoreThreads + threadIdx.x;
   for (int64_t i = g0; i < a.n; i += step) {
-    a.wf[i] = a.swf[i];
-    a.type[i] = a.stype[i];
-    a.est[i] = a.sest[i];
+    const int32_t wf = a.swf[i], type = a.stype[i], loc = a.sloc[i];
+    const int64_t est = a.sest[i];
+    a.wf[i] = wf;
+    a.type[i] = type;
+    a.est[i] = est;
     a.done[i] = a.sdone[i];
-    a.loc[i] = a.sloc[i];
+    a.loc[i] = loc;
+    a.att[i] = att_pack(wf, type, est, loc);
     const int32_t x0 = a.soff[i], x1 = a.soff[i + 1];
     b |= x1 < x0 || (i == 0 && x0 != 0) || (i == a.n - 1 && int64_t(x1) != a.n_edges);
     a.off[i + 1] = a.base + x1;
@@ -234,7 +239,7 @@ void nalar_store_destroy(nalar_store* st) {
   (void)hipSetDevice(policy_device(st->h));
   (void)hipStreamSynchronize(policy_stream(st->h));
   for (void* p : {static_cast<void*>(st->wf), static_cast<void*>(st->type), static_cast<void*>(st->est),
-                  static_cast<void*>(st->done), static_cast<void*>(st->loc), static_cast<void*>(st->dep_off),
+                  static_cast<void*>(st->done), static_cast<void*>(st->loc), static_cast<void*>(st->att), static_cast<void*>(st->dep_off),
                   static_cast<void*>(st->dep_idx), static_cast<void*>(st->deadline),
                   static_cast<void*>(st->inst_type), static_cast<void*>(st->inst_load),
                   static_cast<void*>(st->inst_speed), static_cast<void*>(st->rem), static_cast<void*>(st->fl),
@@ -272,6 +277,7 @@ int nalar_store_append(nalar_store* st, int64_t n_new, int64_t n_new_edges, cons
     if (e == hipSuccess) { c0 = st->capN; e = grow(st->est, c0, nc, N, s); }
     if (e == hipSuccess) { c0 = st->capN; e = grow(st->done, c0, nc, N, s); }
     if (e == hipSuccess) { c0 = st->capN; e = grow(st->loc, c0, nc, N, s); }
+    if (e == hipSuccess) { c0 = st->capN; e = grow(st->att, c0, nc, N, s); }
     if (e == hipSuccess) { c0 = st->capN + 1; e = grow(st->dep_off, c0, nc + 1, N + 1, s); }
     if (e != hipSuccess) return store_fail(st, e, "store grow");
     st->capN = nc;
@@ -303,7 +309,7 @@ int nalar_store_append(nalar_store* st, int64_t n_new, int64_t n_new_edges, cons
   if (n_new > 0) {
     const AppendArgs aa{st->wf + N, st->type + N, st->est + N, st->done + N, st->loc + N, st->dep_off + N,
                         st->dep_idx + E, wf, type, est_us, done, loc, dep_off, dep_idx, n_new, n_new_edges,
-                        int32_t(E), st->bad, int32_t(N), st->hv, st->hv_n, st->capH};
+                        int32_t(E), st->bad, st->att + N, int32_t(N), st->hv, st->hv_n, st->capH};
     hipLaunchKernelGGL(k_store_append, dim3(grid_for(n_new > n_new_edges ? n_new : n_new_edges)),
                        dim3(kStoreThreads), 0, s, aa);
     e = hipGetLastError();
@@ -421,7 +427,7 @@ int nalar_store_pass(nalar_store* st, int64_t now_us, int64_t migration_cost_us,
   else if (st->W < st->W_prev || st->M < st->M_prev) st->last_fallback = NALAR_STORE_FULL_SHRUNK;
   else {
     IncStore is{st->n_prev, st->log, st->n_log, st->rem, st->fl, st->mxA, st->cntA, st->light,
-                      st->heavy, st->rbits, st->hv, st->hv_n, st->capH, st->rheavy, st->ic,
+                      st->heavy, st->att, st->rbits, st->hv, st->hv_n, st->capH, st->rheavy, st->ic,
                 st->rounds};
     rc = policy_pass_incremental(st->h, &p, r, is);
     st->rounds = is.rounds;
