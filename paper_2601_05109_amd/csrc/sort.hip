@@ -709,16 +709,24 @@ __device__ inline int64_t output_key(const SortArgs& a, int64_t g) {
 // times the threads and the LDS) for the few bins holding more: the bins hold up to
 // kBinAlloc records, so that a ready set whose keys moved since the splitters
 // were taken (a whole workflow's futures shifting together) still fits.
-constexpr int kBinBigThreads = 4 * kBinThreads;
+// With workflow ties (more LDS: three workgroups a CU instead of four) or more
+// bins than the chip holds at once, a bin gets twice the threads: 31 -> 26 us at
+// 0.95M ready futures with ties, 60 -> 51 us at 2.3M, 58 -> 54 us for 1.55M over
+// 2,048 bins without; but 25 -> 27 us for 1M over 1,024 bins, which are all in
+// work together either way (1,024 threads: 40 to 86 us).
+constexpr int kBinWideThreads = 512;
+constexpr int kBinNarrow = 1024;
+constexpr int kBinBigThreads = 1024;
 constexpr int kBinBigCap = 4 * kBinCap;
 static_assert(kBinBigCap >= kBinAlloc, "the big-bin kernel holds a full bin");
-constexpr int kBinJ = (kBinCap + kBinThreads - 1) / kBinThreads;  // items per lane (both kernels)
-static_assert(kBinJ * kBinBigThreads >= kBinBigCap, "items per lane of the big-bin kernel");
 constexpr int kBinSub = 1024;
 constexpr int kBinSubLog = 10;
 static_assert(kBinSub == 1 << kBinSubLog && kBinSub % kBinBigThreads == 0, "sub-buckets");
 
-constexpr int kBinRun = 32;
+// Mates counted one by one up to here, beyond by the network: at 48 futures per
+// key (children created alike) a bin's few networks of 33 to 64 entries cost more
+// than the whole rest (a store tick 200 -> 240 us); counted, 203 us.
+constexpr int kBinRun = 128;
 constexpr int kBinCrowdMax = kBinBigCap / (kBinRun + 1) + 1;  // crowded sub-buckets a bin can hold
 
 template <int NW>
@@ -833,6 +841,7 @@ template <int T, int LC>
 __device__ void bin_sort_one(const SortArgs& a, const BucketArgs& bk, int b, int n, const BinLds<T / kWave>& L) {
   constexpr int kBinThreads = T;
   constexpr int kBinWaves = T / kWave;
+  constexpr int kBinJ = (LC + T - 1) / T;  // items per lane
   const int cap = bk.cap;
   const int32_t* tw = a.tie_wf;
   int64_t* s_key = L.key;
@@ -1031,15 +1040,16 @@ __device__ void bin_sort_one(const SortArgs& a, const BucketArgs& bk, int b, int
 // k_bin_sort_big.  Workgroup 0 settles and publishes the status and range,
 // and the size of the largest bin (in max_bucket), from which the host plans
 // the next pass's bin capacity.
-__global__ __launch_bounds__(kBinThreads) void k_bin_sort(SortArgs a, BucketArgs bk) {
+template <int T>
+__global__ __launch_bounds__(T) void k_bin_sort(SortArgs a, BucketArgs bk) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int NW = kBinThreads / kWave;
+  constexpr int NW = T / kWave;
   const BinLds<NW> L = carve_bin<NW>(smem, kBinCap, a.tie_wf != nullptr);
   const int b = blockIdx.x;
   if (b == 0) {
     __shared__ uint32_t s_mx[NW];
     uint32_t mx = 0;
-    for (int i = int(threadIdx.x); i < bk.nb; i += kBinThreads) mx = bk.cnt[i] > mx ? bk.cnt[i] : mx;
+    for (int i = int(threadIdx.x); i < bk.nb; i += T) mx = bk.cnt[i] > mx ? bk.cnt[i] : mx;
     mx = uint32_t(wave_max_i64(int64_t(mx)));
     if (lane_id() == 0) s_mx[threadIdx.x / kWave] = mx;
     __syncthreads();
@@ -1065,7 +1075,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_sort(SortArgs a, BucketArgs
   const uint32_t nraw = bk.cnt[b];
   const int n = int(nraw < uint32_t(bk.cap) ? nraw : uint32_t(bk.cap));
   if (n > kBinCap) return;
-  bin_sort_one<kBinThreads, kBinCap>(a, bk, b, n, L);
+  bin_sort_one<T, kBinCap>(a, bk, b, n, L);
 }
 
 // The bins of more than kBinCap records: every workgroup lists them in bin
@@ -1555,8 +1565,13 @@ hipError_t launch_bucket_sort(hipStream_t s, const SortArgs& a, const BucketArgs
 }
 
 hipError_t launch_bin_sort(hipStream_t s, const SortArgs& a, const BucketArgs& bk) {
-  hipLaunchKernelGGL(k_bin_sort, dim3(bk.nb), dim3(kBinThreads),
-                     bin_lds_bytes<kBinThreads / kWave>(kBinCap, a.tie_wf != nullptr), s, a, bk);
+  const bool tie = a.tie_wf != nullptr;
+  if (tie || bk.nb > kBinNarrow)
+    hipLaunchKernelGGL(k_bin_sort<kBinWideThreads>, dim3(bk.nb), dim3(kBinWideThreads),
+                       bin_lds_bytes<kBinWideThreads / kWave>(kBinCap, tie), s, a, bk);
+  else
+    hipLaunchKernelGGL(k_bin_sort<kBinThreads>, dim3(bk.nb), dim3(kBinThreads),
+                       bin_lds_bytes<kBinThreads / kWave>(kBinCap, tie), s, a, bk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || bk.cap <= kBinCap) return e;
   hipLaunchKernelGGL(k_bin_sort_big, dim3(kBinBigGroups), dim3(kBinBigThreads),
@@ -1569,9 +1584,13 @@ hipError_t prepare_sort_kernels() {
     const hipError_t eg = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, int(4 * kGroupWMax));
     if (eg != hipSuccess) return eg;
   }
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bin_sort),
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bin_sort<kBinThreads>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
                                      int(bin_lds_bytes<kBinThreads / kWave>(kBinCap, true)));
+  if (e != hipSuccess) return e;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bin_sort<kBinWideThreads>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize,
+                          int(bin_lds_bytes<kBinWideThreads / kWave>(kBinCap, true)));
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bin_sort_big),
                              hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -210,3 +210,34 @@ def test_grouping_by_many_workflows(policy, W, n):  # noqa: F811
     r = wl.relabel(q, perm)
     for rep in range(2):
         check(policy, r, f"grouped W={W} n={n} pass {rep}", flags=0)
+
+
+# ---------------------------------------------------------------- bin sort
+
+@pytest.mark.parametrize("equal", [1, 31, 33, 127, 128, 129, 300])
+def test_bin_sort_equal_keys(equal):
+    """Ready sets in which `equal` futures share each key, around the counts at
+    which a bin ranks mates one by one or by a network, over enough futures for
+    the bins of a full pass (1.2M: more bins than workgroups resident) and of an
+    incremental store pass (ties by workflow and id)."""
+    n = 1_200_000
+    rng = np.random.default_rng(equal)
+    W = 200
+    wf = np.repeat(np.arange(W), n // W).astype(np.int32)
+    p = _independent(n, 24, 5, equal)
+    p = p.copy(wf=wf, deadline_us=np.full(W, p.now_us + 10**7, np.int64),
+               est_us=(rng.permutation(n) // equal).astype(np.int64))
+    with nalar.Policy() as pol:
+        for rep in range(2):
+            check(pol, p, f"{equal} equal keys pass {rep}")
+    q = _independent(90_000, 24, 5, equal)
+    q = q.copy(wf=rng.integers(0, W, 90_000).astype(np.int32), deadline_us=np.full(W, q.now_us + 10**7, np.int64),
+               est_us=(rng.permutation(90_000) // equal).astype(np.int64), wf_contiguous=False)
+    with nalar.Policy() as pol, nalar.Store(pol) as st:
+        prev = feed(st, q, 0, None)
+        store_pass(pol, st, q)
+        for tick in range(2):
+            q = _extended(q, rng.choice(q.n_nodes, 50, replace=False), rng.integers(0, q.n_nodes, 60), tick)
+            prev = feed(st, q, *prev)
+            g, inc = store_pass(pol, st, q)
+            assert_parity(g, oracle.run(q), f"{equal} equal keys, store tick {tick}, incremental {inc}")
