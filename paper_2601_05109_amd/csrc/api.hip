@@ -11,6 +11,8 @@
 //               futures, at most 128 instances) also validation, workflow
 //               bounds, the instance table and the reset of the next pass's
 //               control block and bucket counters
+//               (a large snapshot the library grouped itself takes [records],
+//               sweep by records and [ready] instead: grouped.hip)
 //   sort     -> bucketed: the sweep has dropped every ready future into a
 //               bucket of a key range planned from the previous pass, and one
 //               kernel (two for many buckets) orders each bucket and writes it
@@ -62,7 +64,7 @@ struct Arena {
   int32_t* stg_route = nullptr;
   int64_t* stg_cost = nullptr;
   int64_t* stg_oslack = nullptr;  // slack by position when the order key is not the slack
-  uint64_t* skey[2] = {nullptr, nullptr};
+  uint64_t* skey[2] = {nullptr, nullptr};  // one after the other (the record sweep's records before the sort)
   uint32_t* spay[2] = {nullptr, nullptr};
   uint64_t* slb = nullptr;
   uint32_t* gkey[2] = {nullptr, nullptr};
@@ -78,6 +80,7 @@ struct Arena {
   uint8_t* g_dn = nullptr;
   uint8_t* g_nr = nullptr;
   int32_t* g_front[2] = {nullptr, nullptr};
+  uint64_t* rbits = nullptr;      // [N / 64] ready futures by id (record sweep)
   uint64_t* done_bits = nullptr;  // [N / 64] the done flags, one bit per future
   uint32_t* bcnt[2] = {nullptr, nullptr};  // bucket counters, by pass parity
   BucketSlot* bslot = nullptr;
@@ -138,6 +141,8 @@ struct nalar_policy {
   bool bucket_relaxed = false;   // the last pass tried fewer buckets
   int split_nb = 0;              // bins the current splitters are for (0: none)
   int split_cur = 0;             // the splitter buffer the next pass reads
+  int rec_skip = 0;              // passes left before the record sweep is tried again
+  int rec_backoff = 1;
   int bin_skip = 0;              // passes left before bins are tried again
   int bin_backoff = 1;
   bool split_any = false;        // splitters for any ready count, any sweep (graph store)
@@ -195,7 +200,8 @@ size_t carve(Arena& a, char* base, int64_t N, int64_t W, int64_t B, int64_t Rec)
   a.stg_route = reinterpret_cast<int32_t*>(take(4 * size_t(n1)));
   a.stg_ready = reinterpret_cast<uint8_t*>(take(size_t(n1)));
   a.stg_oslack = reinterpret_cast<int64_t*>(take(8 * size_t(n1)));
-  for (int i = 0; i < 2; ++i) a.skey[i] = reinterpret_cast<uint64_t*>(take(8 * size_t(n1)));
+  a.skey[0] = reinterpret_cast<uint64_t*>(take(16 * size_t(n1)));  // both together: a record per future
+  a.skey[1] = a.skey[0] ? a.skey[0] + n1 : nullptr;
   for (int i = 0; i < 2; ++i) a.spay[i] = reinterpret_cast<uint32_t*>(take(4 * size_t(n1)));
   for (int i = 0; i < 2; ++i) a.gkey[i] = reinterpret_cast<uint32_t*>(take(4 * size_t(n1)));
   for (int i = 0; i < 2; ++i) a.gpay[i] = reinterpret_cast<uint32_t*>(take(4 * size_t(n1)));
@@ -206,6 +212,7 @@ size_t carve(Arena& a, char* base, int64_t N, int64_t W, int64_t B, int64_t Rec)
   a.g_dn = reinterpret_cast<uint8_t*>(take(size_t(n1)));
   a.g_nr = reinterpret_cast<uint8_t*>(take(size_t(n1)));
   a.done_bits = reinterpret_cast<uint64_t*>(take(8 * size_t((n1 + 63) / 64)));
+  a.rbits = reinterpret_cast<uint64_t*>(take(8 * size_t((n1 + 63) / 64)));
   const int64_t b1 = B > 0 ? B : 0;
   for (int i = 0; i < 2; ++i) a.bcnt[i] = reinterpret_cast<uint32_t*>(take(4 * size_t(b1 + 1)));
   const int64_t r1 = Rec > b1 * kBucketCap ? Rec : b1 * kBucketCap;
@@ -502,6 +509,8 @@ int nalar_policy_create(const nalar_policy_config* cfg, nalar_policy** out) {
   if (e != hipSuccess) return bail(e, "hipFuncSetAttribute");
   e = prepare_sort_kernels();
   if (e != hipSuccess) return bail(e, "hipFuncSetAttribute(sort)");
+  e = prepare_rec_kernels();
+  if (e != hipSuccess) return bail(e, "hipFuncSetAttribute(records)");
   e = prepare_inc_kernels();
   if (e != hipSuccess) return bail(e, "hipFuncSetAttribute(incremental)");
   e = hipHostMalloc(reinterpret_cast<void**>(&h->host), sizeof(HostStatus), hipHostMallocCoherent);
@@ -726,6 +735,12 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
     pos_of_node = A.pos_of_node;
   }
 
+  // The record sweep (grouped.hip): a snapshot the library groups itself, of
+  // workflows beyond the wave sweep, with bins planned; not where a testing flag
+  // asks for one of the block sweep's forms, and not for a while after a snapshot
+  // it could not take (ids not in topological order).
+  const bool rec = N > 0 && bk.bins && node_of_pos && !sh.wave_path && own_splitters && h->rec_skip == 0 &&
+                   !(h->flags & (NALAR_FORCE_GLOBAL_SWEEP | NALAR_FORCE_LEVEL_SWEEP));
   SweepArgs sw{};
   BlockSweepArgs ba{};
   if (N > 0) {
@@ -760,7 +775,27 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
       ba.plog_lp = reinterpret_cast<int32_t*>(static_cast<char*>(as.plog) + align_up(size_t(as.plog_cap) * 8, 256));
       ba.plog_cap = as.plog_cap;
     }
-    NALAR_LAUNCH("sweep", launch_sweep(s, sw, ba, sh));
+    if (rec) {
+      RecArgs ra{pd, A.wf_off, pos_of_node, reinterpret_cast<const uint32_t*>(A.done_bits),
+                 reinterpret_cast<uint4*>(A.skey[0]), A.rbits, A.g_mx, ctrl};
+      NALAR_LAUNCH("records", launch_rec(s, ra));
+      NALAR_LAUNCH("sweep", launch_sweep_rec(s, ra, h->cus));
+      IncArgs ia{};
+      ia.p = pd;
+      ia.rem_out = r->rem_us;
+      ia.rem_pos = A.g_mx;
+      ia.pos_of_node = pos_of_node;
+      ia.rbits = A.rbits;
+      ia.ctrl = ctrl;
+      ia.itab = A.itab;
+      ia.bk = bk;
+      ia.bk_clear = A.bcnt[nxt];
+      ia.bk_clear_n = A.capB > 0 ? A.capB : 0;
+      ia.stg_oslack = A.stg_oslack;
+      NALAR_LAUNCH("ready", launch_inc_ready(s, ia, h->cus, true));
+    } else {
+      NALAR_LAUNCH("sweep", launch_sweep(s, sw, ba, sh));
+    }
     as.bcnt_clean[nxt] = true;  // the sweep cleared them for the next pass
   }
 
@@ -772,7 +807,9 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
   sa.stg_ready = A.stg_ready;
   sa.stg_route = A.stg_route;
   sa.stg_cost = A.stg_cost;
-  sa.node_of_pos = node_of_pos;
+  sa.node_of_pos = rec ? nullptr : node_of_pos;  // the records' ready futures are binned by id
+  sa.tie_wf = rec ? p->wf : nullptr;
+  sa.tie_packed = W <= kPackWf ? 1 : 0;
   sa.out_slack = ((policy & (NALAR_ORDER_LPT | NALAR_ORDER_SRTF)) || p->wf_priority) ? A.stg_oslack : nullptr;
   sa.span = N;
   for (int i = 0; i < 2; ++i) {
@@ -833,7 +870,12 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
       // into; the next pass's control block and counters are reset again too.
       __atomic_store_n(&h->host->status, 0xFFFFFFFFu, __ATOMIC_RELEASE);
       tiled = true;
-      if (bk.bins) {  // a bin overflowed: new splitters come from the tiled sort; back off
+      sa.node_of_pos = node_of_pos;  // the sweep below stages by position
+      sa.tie_wf = nullptr;
+      if (rec && __atomic_load_n(&h->host->unordered, __ATOMIC_ACQUIRE) != 0) {
+        h->rec_skip = h->rec_backoff;
+        h->rec_backoff = h->rec_backoff < 64 ? 2 * h->rec_backoff : 64;
+      } else if (bk.bins) {  // a bin overflowed: new splitters come from the tiled sort; back off
         h->bin_max = 0;
         h->bin_skip = h->bin_backoff;
         h->bin_backoff = h->bin_backoff < 64 ? 2 * h->bin_backoff : 64;
@@ -856,6 +898,7 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
       NALAR_LAUNCH("sweep", launch_sweep(s, sw, ba, sh));
     } else if (bk.bins) {
       h->bin_backoff = 1;
+      if (rec) h->rec_backoff = 1;
       h->bin_max = __atomic_load_n(&h->host->max_bucket, __ATOMIC_ACQUIRE);
     } else {
       h->bucket_backoff = 1;
@@ -1127,6 +1170,7 @@ int nalar_policy_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r) 
   if (!bk.bins) bk = plan_buckets(h, N, p->wf_priority != nullptr, sh.wave_path != 0);
   if (h->bucket_skip > 0) --h->bucket_skip;
   if (h->bin_skip > 0) --h->bin_skip;
+  if (h->rec_skip > 0) --h->rec_skip;
   rc = ensure_capacity(h, N, W, bk.nb, records_of(bk));
   if (rc != NALAR_OK) return rc;
   if (!sh.wave_path && !(h->flags & NALAR_FORCE_LEVEL_SWEEP)) {

@@ -853,7 +853,10 @@ struct ReadyAcc {
 };
 
 // One chunk: the n (at most kReadyChunk) listed futures from `first` on.  Every
-// thread of the workgroup calls it, after a barrier behind the listing.
+// thread of the workgroup calls it, after a barrier behind the listing.  kStore:
+// the incremental pass (rem by id, attribute records), else the full pass by
+// records (rem by position, the caller's attribute arrays).
+template <bool kStore>
 __device__ inline void ready_chunk(const IncArgs& a, const ReadyLds& S, int first, int n, ReadyAcc& acc) {
   constexpr int T = kReadyThreads;
   const int tid = threadIdx.x;
@@ -870,8 +873,10 @@ __device__ inline void ready_chunk(const IncArgs& a, const ReadyLds& S, int firs
   for (int j = 0; j < kReadyPer; ++j) v[j] = j * T + tid < n ? S.list[first + j * T + tid] : -1;
 #pragma unroll
   for (int j = 0; j < kReadyPer; ++j) {
-    at[j] = a.att[v[j] >= 0 ? v[j] : 0];
-    key[j] = a.rem[v[j] >= 0 ? v[j] : 0];
+    const int32_t u = v[j] >= 0 ? v[j] : 0;
+    at[j] = kStore ? a.att[u] : att_pack(a.p.wf[u], a.p.type[u], a.p.est[u], a.p.loc[u]);
+    // (by records: the caller's copy, which this workgroup has just written)
+    key[j] = kStore ? a.rem[u] : (a.rem_out ? a.rem_out[u] : a.rem_pos[a.pos_of_node[u]]);
   }
 #pragma unroll
   for (int j = 0; j < kReadyPer; ++j) {
@@ -934,14 +939,15 @@ __device__ inline void ready_chunk(const IncArgs& a, const ReadyLds& S, int firs
   }
 }
 
+template <bool kStore>
 __global__ __launch_bounds__(kReadyThreads) void k_inc_ready(IncArgs a) {
   constexpr int T = kReadyThreads;
   const int tid = threadIdx.x;
   for (int64_t i = int64_t(blockIdx.x) * T + tid; i < a.bk_clear_n; i += int64_t(gridDim.x) * T)
     a.bk_clear[i] = 0;  // the next pass's bin counters
   Ctrl* ctrl = a.ctrl;
-  if (ctrl->status != 0) return;
-  if (blockIdx.x == 0 && tid < kWave) check_rounds(a);
+  if (ctrl->status != 0 || (!kStore && ctrl->unordered != 0)) return;  // written by earlier kernels only
+  if (kStore && blockIdx.x == 0 && tid < kWave) check_rounds(a);
   extern __shared__ __align__(16) unsigned char smem[];
   const int M = int(a.p.M);
   const ReadyLds S = carve_ready(smem, M);
@@ -967,7 +973,7 @@ __global__ __launch_bounds__(kReadyThreads) void k_inc_ready(IncArgs a) {
   const int64_t G = gridDim.x;
   ReadyAcc acc;
   // the ready futures of many dependencies (their own list)
-  const uint32_t nh = a.ic->r_heavy;
+  const uint32_t nh = kStore ? a.ic->r_heavy : 0u;
   for (uint32_t h0 = blockIdx.x; h0 < nh; h0 += uint32_t(G) * T) {
     const uint64_t h = uint64_t(h0) + uint64_t(tid) * uint64_t(G);
     const bool in = h < nh;
@@ -979,23 +985,30 @@ __global__ __launch_bounds__(kReadyThreads) void k_inc_ready(IncArgs a) {
     __syncthreads();
     const int n = s_n;
     if (n >= kReadyChunk) {  // the same on every thread
-      ready_chunk(a, S, n - kReadyChunk, kReadyChunk, acc);
+      ready_chunk<kStore>(a, S, n - kReadyChunk, kReadyChunk, acc);
       if (tid == 0) s_n = n - kReadyChunk;
     }
     __syncthreads();
   }
-  constexpr int kUnits = kReadyStep / kReadyUnit;  // units per step
-  const int64_t units = (N + kReadyUnit - 1) / kReadyUnit;
+  // (by records a unit is a whole step: ids of one workflow lie hundreds apart,
+  // and their rems side by side)
+  constexpr int U = kStore ? kReadyUnit : kReadyStep;
+  constexpr int kUnits = kReadyStep / U;  // units per step
+  const int64_t units = (N + U - 1) / U;
   for (int64_t k0 = 0; int64_t(blockIdx.x) + k0 * G < units; k0 += kUnits) {
     int64_t id[kReadyTake], rv[kReadyTake];
     uint64_t w[kReadyTake];
 #pragma unroll
     for (int j = 0; j < kReadyTake; ++j) {
-      const int64_t k = k0 + j * (T / kReadyUnit) + tid / kReadyUnit;
-      const int64_t u = int64_t(blockIdx.x) + k * G;
-      id[j] = u < units ? u * kReadyUnit + (tid & (kReadyUnit - 1)) : N;
+      const int at = j * T + tid;  // within the step
+      const int64_t u = int64_t(blockIdx.x) + (k0 + at / U) * G;
+      id[j] = u < units ? u * U + at % U : N;
+      if (id[j] > N) id[j] = N;
       w[j] = id[j] < N ? a.rbits[id[j] / kWave] : 0;  // the same on the lanes of the wave below N
-      if (a.rem_out) rv[j] = id[j] < N ? a.rem[id[j]] : 0;
+      if (a.rem_out) {
+        const int64_t x = id[j] < N ? id[j] : 0;
+        rv[j] = kStore ? a.rem[x] : a.rem_pos[a.pos_of_node[x]];
+      }
     }
 #pragma unroll
     for (int j = 0; j < kReadyTake; ++j) {
@@ -1010,12 +1023,12 @@ __global__ __launch_bounds__(kReadyThreads) void k_inc_ready(IncArgs a) {
     __syncthreads();
     const int n = s_n;
     if (n >= kReadyChunk) {  // the same on every thread
-      ready_chunk(a, S, n - kReadyChunk, kReadyChunk, acc);
+      ready_chunk<kStore>(a, S, n - kReadyChunk, kReadyChunk, acc);
       if (tid == 0) s_n = n - kReadyChunk;
     }
     __syncthreads();
   }
-  if (s_n > 0) ready_chunk(a, S, 0, s_n, acc);  // at most kReadyChunk - 1
+  if (s_n > 0) ready_chunk<kStore>(a, S, 0, s_n, acc);  // at most kReadyChunk - 1
   const int64_t mn = wave_min_i64(acc.mn), mx = wave_max_i64(acc.mx), rd = wave_sum_i64(acc.n);
   const int wv = tid / kWave;
   if (lane_id() == 0) {
@@ -1060,8 +1073,12 @@ size_t inc_ready_lds(int64_t M) {
 }
 
 hipError_t prepare_inc_kernels() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_inc_ready),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, int(inc_ready_lds(NALAR_MAX_INSTANCES)));
+  for (const void* k : {reinterpret_cast<const void*>(&k_inc_ready<true>), reinterpret_cast<const void*>(&k_inc_ready<false>)}) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             int(inc_ready_lds(NALAR_MAX_INSTANCES)));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_inc_clear(hipStream_t s, uint32_t* p, int64_t n) {
@@ -1124,11 +1141,15 @@ hipError_t launch_inc_sweep(hipStream_t s, const IncArgs& a, int cus, int rounds
   return hipGetLastError();
 }
 
-hipError_t launch_inc_ready(hipStream_t s, const IncArgs& a, int cus) {
+hipError_t launch_inc_ready(hipStream_t s, const IncArgs& a, int cus, bool records) {
   // one workgroup per CU (their LDS allows no more), fewer for few futures
   int64_t g = (a.p.N + kReadyStep - 1) / kReadyStep;
   if (g > cus) g = cus;
-  hipLaunchKernelGGL(k_inc_ready, dim3(unsigned(g < 1 ? 1 : g)), dim3(kReadyThreads), inc_ready_lds(a.p.M), s, a);
+  const dim3 grid(unsigned(g < 1 ? 1 : g));
+  if (records)
+    hipLaunchKernelGGL(k_inc_ready<false>, grid, dim3(kReadyThreads), inc_ready_lds(a.p.M), s, a);
+  else
+    hipLaunchKernelGGL(k_inc_ready<true>, grid, dim3(kReadyThreads), inc_ready_lds(a.p.M), s, a);
   return hipGetLastError();
 }
 

@@ -276,6 +276,8 @@ struct IncArgs {
   int32_t* light;                // [N] per-round lists
   int32_t* heavy;                // [N]
   const uint4* att;              // [N] att_pack of each future
+  const int64_t* rem_pos;        // full pass by records: [N] rem by position,
+  const int32_t* pos_of_node;    //   and each future's position
   uint64_t* rbits;               // [ceil(N/64)] ready futures with few dependencies, as bits
   const int32_t* hv;             // [hv_cap] futures with more than kIncHeavy dependencies
   const uint32_t* hv_n;          //   and their number
@@ -301,7 +303,9 @@ hipError_t launch_inc_closure(hipStream_t s, const IncArgs& a, int cus, int roun
 hipError_t launch_inc_scan(hipStream_t s, const IncArgs& a, int cus);
 hipError_t launch_inc_sweep(hipStream_t s, const IncArgs& a, int cus, int rounds,
                             void (*mark)(void*, const char*), void* ctx);
-hipError_t launch_inc_ready(hipStream_t s, const IncArgs& a, int cus);
+// records: the full pass behind launch_sweep_rec (p, rem_pos, pos_of_node,
+// rem_out, rbits and the bins of the arguments are used), else the incremental one.
+hipError_t launch_inc_ready(hipStream_t s, const IncArgs& a, int cus, bool records = false);
 
 // The store's side of an incremental pass (defined in api.hip): its buffers,
 // and the pass.  Returns a NALAR_* code, or one of the kIncFallback codes when
@@ -341,6 +345,22 @@ int policy_reserve(nalar_policy* h, int64_t N, int64_t E, int64_t W);
 hipStream_t policy_stream(const nalar_policy* h);
 int policy_device(const nalar_policy* h);
 int policy_fail(nalar_policy* h, int code, const char* msg);
+
+// grouped.hip: records by position and rem by position, for snapshots grouped by
+// the library (the ready kernel of the incremental pass follows).
+struct RecArgs {
+  ProblemDev p;
+  const int32_t* wf_off;        // [W + 1]
+  const int32_t* pos_of_node;   // [N]
+  const uint32_t* done_bits;    // [ceil(N/32)]
+  uint4* rec;                   // [N] by position
+  uint64_t* rbits;              // [ceil(N/64)] ready futures by id
+  int64_t* rem_pos;             // [N] by position
+  Ctrl* ctrl;
+};
+hipError_t prepare_rec_kernels();  // LDS limit (at handle creation)
+hipError_t launch_rec(hipStream_t s, const RecArgs& a);
+hipError_t launch_sweep_rec(hipStream_t s, const RecArgs& a, int cus);
 
 // ingest.hip
 // Validates the futures from v_begin on (and every deadline and instance).

@@ -1069,7 +1069,10 @@ __global__ __launch_bounds__(T) void k_bin_sort(SortArgs a, BucketArgs bk) {
   }
   if (b == 0) {
     settle_range(rl, ctrl, L.F->range, true, a.levels != 0);
-    if (threadIdx.x == 0) publish_range(a.host, overflow ? kStatusTiled : 0u, L.F->range);
+    if (threadIdx.x == 0) {
+      __hip_atomic_store(&a.host->unordered, ctrl->unordered, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      publish_range(a.host, overflow ? kStatusTiled : 0u, L.F->range);
+    }
   }
   if (overflow) return;
   const uint32_t nraw = bk.cnt[b];

@@ -241,3 +241,85 @@ def test_bin_sort_equal_keys(equal):
             prev = feed(st, q, *prev)
             g, inc = store_pass(pol, st, q)
             assert_parity(g, oracle.run(q), f"{equal} equal keys, store tick {tick}, incremental {inc}")
+
+
+# ---------------------------------------------------------------- record sweep
+
+def _grown_workflows(sizes, seed):
+    """Workflows of these sizes with ids by creation, the workflows interleaved:
+    most futures independent, the others on one earlier future (the last one, any,
+    or the first: a hub), some on several, a few on hundreds."""
+    rng = np.random.default_rng(seed)
+    sizes = np.asarray(sizes)
+    W, N = len(sizes), int(sizes.sum())
+    first = np.concatenate([[0], np.cumsum(sizes)])
+    kinds = rng.choice(6, size=N, p=[0.62, 0.12, 0.12, 0.08, 0.055, 0.005])
+    kinds[:sizes[0]] = 1  # one workflow is a single chain: as deep as it is long
+    counts, flat = np.zeros(N, np.int64), []
+    for w in range(W):
+        for i in range(sizes[w]):
+            k = kinds[first[w] + i]
+            if k == 0 or i < 2 and k != 1 or i == 0:
+                continue
+            if k == 1:
+                par = [i - 1]
+            elif k == 2:
+                par = [int(rng.integers(0, i))]
+            elif k == 3:
+                par = [0]
+            elif k == 4:
+                par = [int(x) for x in rng.integers(0, i, int(rng.integers(2, 6)))]
+            else:
+                par = [int(x) for x in rng.integers(0, i, int(rng.integers(33, 300)))]
+            counts[first[w] + i] = len(par)
+            flat += [int(first[w]) + q for q in par]
+    M, K, now = 40, 6, 5_000
+    p = wl.Problem(f"grown-{W}", now, 150_000, np.repeat(np.arange(W, dtype=np.int32), sizes),
+                   rng.integers(0, K, N).astype(np.int32), rng.integers(0, 10**6, N).astype(np.int64),
+                   (rng.random(N) < 0.1).astype(np.uint8),
+                   np.where(rng.random(N) < 0.5, rng.integers(0, M, N), -1).astype(np.int32),
+                   np.concatenate([[0], np.cumsum(counts)]).astype(np.int32), np.asarray(flat, np.int32),
+                   (now + rng.integers(0, 10**7, W)).astype(np.int64), (np.arange(M) % K).astype(np.int32),
+                   rng.integers(0, 10**6, M).astype(np.int64), rng.integers(300, 3000, M).astype(np.int32),
+                   wf_contiguous=True)
+    slots = np.argsort(rng.permutation(N) // 3, kind="stable")  # any interleaving
+    owner = p.wf[slots]
+    perm = np.argsort(owner, kind="stable")
+    return wl.relabel(p, perm), p
+
+
+@pytest.mark.parametrize("W,n", [(230, 520), (120, 1024), (118, 1025), (60, 2048), (59, 2049), (40, 3073), (9, 14_000),
+                                 (9, 19_457), (9, 21_505), (300, 530)])
+def test_record_sweep(W, n):
+    """Workflows around whole chunks of 1,024 positions and around the chunks kept
+    in LDS (19, or 9 for more workflows than the chip holds at once; the last size:
+    two such workflows among 298 small ones), ids by creation: the first pass sorts in tiles, the next ones take the record sweep; under other
+    policies; with one estimate too large to add up; and with ids that are not in
+    topological order, which go back to the block sweep."""
+    sizes = np.full(W, n)
+    if W > 256:
+        sizes[1:3] = 10_500
+    p, grouped = _grown_workflows(sizes, W + n)
+    with nalar.Policy() as pol:
+        pol.set_timing(True)
+        for rep, policy in enumerate((0, 0, nalar.NALAR_ORDER_LPT, nalar.NALAR_ORDER_SRTF | nalar.NALAR_ROUTE_STATEFUL)):
+            check(pol, p, f"records W={W} n={n} pass {rep}", policy=policy)
+            assert rep not in (1, 2) or "records" in [k for k, _ in pol.timing()]
+        pol.set_timing(False)
+        q = p.copy()
+        q.dep_idx[np.flatnonzero(np.diff(q.dep_off) == 1)[5]] = 0 if q.wf[0] != q.wf[-1] else 1
+        check(pol, q, f"records W={W} n={n} foreign dependency")
+        check(pol, p, f"records W={W} n={n} after it")
+        rng = np.random.default_rng(n)
+        mixed = wl.relabel(grouped, rng.permutation(p.n_nodes))
+        for rep in range(4):
+            check(pol, mixed if rep % 2 == 0 else p, f"records W={W} n={n} order {rep}")
+    with nalar.Policy() as pol:
+        for rep in range(2):
+            dp = nalar.DeviceProblem.from_host(p)
+            out = nalar.DeviceResult.alloc(dp.n_nodes, rem=False)
+            assert pol.run_pass(dp, out) == nalar.NALAR_OK
+            o = oracle.run(p)
+            R = out.n_ready
+            assert R == o.n_ready and np.array_equal(out.order[:R].cpu().numpy(), o.order)
+            assert np.array_equal(out.cost[:R].cpu().numpy(), o.cost)
