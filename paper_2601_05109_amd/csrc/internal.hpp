@@ -386,7 +386,7 @@ hipError_t prepare_sort_kernels();  // LDS limits of the sort kernels (at handle
 hipError_t launch_splitters(hipStream_t s, const SortArgs& a);
 hipError_t launch_slack_sort(hipStream_t s, const SortArgs& a, int first_pass, int last_pass,
                              void (*mark)(void*, const char*), void* ctx);
-// The grouped ids end in pay[0] whatever npass (else in pay[(npass - 1) & 1]).
+// The grouped ids end in pay[0] (else in pay[(npass - 1) & 1]).
 bool group_places_first(const GroupArgs& a);
 hipError_t launch_group(hipStream_t s, const GroupArgs& a, void (*mark)(void*, const char*),
                         void* ctx);

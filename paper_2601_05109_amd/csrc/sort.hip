@@ -1185,122 +1185,22 @@ __global__ __launch_bounds__(kSortThreads) void k_slack_pass(SortArgs a, int pas
   }
 }
 
-// Grouping by workflow in one digit (at most 256 workflows), without the
-// onesweep look-back: its tiles wait on each other in a chain, about 40 ns
-// each, which at 12M futures (3,000 tiles) costs more than the data does.
-// Three kernels instead, each parallel over tiles or workflows:
-//   count  per tile of kSortTile ids, the futures of each workflow
-//          (workflow-major, so that a workflow's counts are contiguous);
-//   scan   per workflow, its tiles' counts into offsets, and its total;
-//   place  per tile, the workflows' starts from the totals, then each
-//          future's stable rank in its tile by ballots, its position =
-//          start + tile offset + rank, and both maps.
-// The counts take the first key buffer, the totals the second.
-constexpr int kGroup1Items = kSortTile / kSortThreads;
-
-__global__ __launch_bounds__(kSortThreads) void k_group1_count(GroupArgs a) {
-  __shared__ uint32_t H[kRadixBuckets];
-  if (a.ctrl->status) return;
-  const int64_t N = a.p.N;
-  const int64_t ntiles = (N + kSortTile - 1) / kSortTile;
-  const int64_t tile = blockIdx.x;
-  H[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t t0 = tile * kSortTile;
-  uint32_t d[kGroup1Items];
-#pragma unroll
-  for (int j = 0; j < kGroup1Items; ++j) {
-    const int64_t i = t0 + j * kSortThreads + threadIdx.x;
-    d[j] = i < N ? uint32_t(a.p.wf[i]) & (kRadixBuckets - 1) : kRadixBuckets;
-  }
-#pragma unroll
-  for (int j = 0; j < kGroup1Items; ++j)
-    if (d[j] < kRadixBuckets) atomicAdd(&H[d[j]], 1u);
-  __syncthreads();
-  a.key[0][int64_t(threadIdx.x) * ntiles + tile] = H[threadIdx.x];
-}
-
-__global__ __launch_bounds__(kSortThreads) void k_group1_scan(GroupArgs a) {
-  __shared__ uint32_t s_tmp[kSortThreads / kWave + 2];
-  __shared__ uint32_t s_sum;
-  if (a.ctrl->status) return;
-  const int64_t ntiles = (a.p.N + kSortTile - 1) / kSortTile;
-  uint32_t* row = a.key[0] + int64_t(blockIdx.x) * ntiles;
-  uint32_t carry = 0;
-  for (int64_t t0 = 0; t0 < ntiles; t0 += kSortThreads) {
-    const int64_t t = t0 + threadIdx.x;
-    const uint32_t x = t < ntiles ? row[t] : 0u;
-    const uint32_t ex = block_excl_scan(x, s_tmp);
-    if (t < ntiles) row[t] = carry + ex;
-    if (threadIdx.x == kSortThreads - 1) s_sum = ex + x;
-    __syncthreads();
-    carry += s_sum;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) a.key[1][blockIdx.x] = carry;
-}
-
-__global__ __launch_bounds__(kSortThreads) void k_group1_place(GroupArgs a) {
-  __shared__ uint32_t s_tmp[kSortThreads / kWave + 2];
-  __shared__ uint32_t base[kRadixBuckets];   // first position of each workflow, then of its part of this tile
-  __shared__ uint32_t wcnt[kSortThreads / kWave][kRadixBuckets];  // this round's futures per wave and workflow
-  __shared__ uint32_t run[kRadixBuckets];    // this tile's futures per workflow in earlier rounds
-  if (a.ctrl->status) return;
-  const int64_t N = a.p.N;
-  const int64_t ntiles = (N + kSortTile - 1) / kSortTile;
-  const int64_t tile = blockIdx.x;
-  const int tid = threadIdx.x, wv = tid / kWave;
-  {
-    const uint32_t tot = a.key[1][tid];
-    const uint32_t start = block_excl_scan(tot, s_tmp);
-    if (tile == 0 && tid <= a.p.W) a.wf_off[tid] = int32_t(start);
-    if (tile == 0 && tid == kSortThreads - 1 && a.p.W == kRadixBuckets) a.wf_off[kRadixBuckets] = int32_t(N);
-    base[tid] = start + a.key[0][int64_t(tid) * ntiles + tile];
-    run[tid] = 0;
-    for (int w = 0; w < kSortThreads / kWave; ++w) wcnt[w][tid] = 0;
-  }
-  __syncthreads();
-  const int64_t t0 = tile * kSortTile;
-  for (int j = 0; j < kGroup1Items; ++j) {
-    const int64_t i = t0 + j * kSortThreads + tid;
-    const bool in = i < N;
-    const uint32_t d = in ? uint32_t(a.p.wf[i]) & (kRadixBuckets - 1) : 0u;
-    uint64_t m = ballot(in);  // the wave's lanes holding the same workflow
-#pragma unroll
-    for (int bit = 0; bit < kRadixBits; ++bit) {
-      const uint64_t b = ballot(in && ((d >> bit) & 1u));
-      m &= ((d >> bit) & 1u) ? b : ~b;
-    }
-    if (in && lanes_below(m) == 0) wcnt[wv][d] = uint32_t(__popcll(m));
-    __syncthreads();
-    if (in) {
-      uint32_t r = run[d] + lanes_below(m);
-      for (int w = 0; w < wv; ++w) r += wcnt[w][d];
-      const uint32_t q = base[d] + r;
-      a.pay[0][q] = uint32_t(i);
-      a.pos_of_node[i] = int32_t(q);
-    }
-    __syncthreads();
-    {
-      uint32_t s = 0;
-      for (int w = 0; w < kSortThreads / kWave; ++w) {
-        s += wcnt[w][tid];
-        wcnt[w][tid] = 0;
-      }
-      run[tid] += s;
-    }
-    __syncthreads();
-  }
-}
-
-// Grouping by workflow for more than kRadixBuckets workflows, up to
-// kGroupWMax, in three launches like the ones above: a tile's counts are one
-// LDS word per workflow, its row of the count matrix holds one word per
-// workflow, and the scan runs down the matrix's columns.  The tile grows with
-// the workflows (at least half as many ids), so the matrix stays below two words
-// per id.  Inside a tile the stable rank comes from ballots over the workflow's
-// bits, per row of 64 ids and wave in parallel; only the addition of a row's
-// counts to the running ones is in order (waves in turn).
+// Grouping by up to kGroupWMax workflows, without the onesweep look-back: its
+// tiles wait on each other in a chain, about 40 ns each, which at 12M futures
+// (3,000 tiles) costs more than the data does.  Three kernels instead, each
+// parallel over tiles or workflows:
+//   count  per tile of ids, the futures of each workflow (LDS), one row of a
+//          matrix of tiles by workflows;
+//   scan   down the matrix's columns: each workflow's counts into offsets, and
+//          its total;
+//   place  per tile, the workflows' starts from the totals, then each future's
+//          stable rank in its tile, its position = start + tile offset + rank,
+//          and both maps.
+// The tile grows with the workflows (at least half as many ids), so the matrix
+// stays below two words per id, and with the ids, so that the scan stays short.
+// Inside a tile the stable rank comes from ballots over the workflow's bits, per
+// row of 64 ids and wave in parallel; only the addition of a row's counts to the
+// running ones is in order (waves in turn).
 //
 // Bound by latency at the sizes this serves: 131,072 ids in creation order over
 // 4,096 workflows took 48 us as a histogram, two look-back digit passes and a
@@ -1311,13 +1211,16 @@ constexpr int kGroupWWaves = kGroupWThreads / kWave;
 constexpr int kGroupWRows = 4;                                      // rows of 64 ids per wave and sub-tile
 constexpr int kGroupWSub = kGroupWThreads * kGroupWRows;            // ids per sub-tile
 constexpr int64_t kGroupWMax = 16384;                               // LDS: 64 KB of counts
-constexpr int kGroupWCols = 64, kGroupWSegs = 16, kGroupWPer = 8;   // column scan: 16 segments of 8 tiles
+constexpr int64_t kGroupWTiles = 2048;                              // tiles before they grow
+// column scan: workflows by segments of kGroupWPer tiles; more segments for few
+// workflows, whose columns are long
+constexpr int kGroupWScan = 1024, kGroupWCols = 64, kGroupWFewCols = 4, kGroupWPer = 8;
 
 // Ids per tile, or 0 when this grouping does not apply.
 int64_t groupw_tile(int64_t N, int64_t W, int64_t cap_n) {
-  if (W <= kRadixBuckets || W > kGroupWMax || W > cap_n) return 0;
+  if (W > kGroupWMax || W > cap_n) return 0;
   int64_t tile = kGroupWSub;
-  while (tile * 2 < W) tile *= 2;
+  while (tile * 2 < W || (N > tile * kGroupWTiles && tile < kGroupWMax)) tile *= 2;
   const int64_t tiles = (N + tile - 1) / tile;
   return tiles * W <= 2 * cap_n ? tile : 0;
 }
@@ -1348,17 +1251,20 @@ __global__ __launch_bounds__(kGroupWThreads) void k_groupw_count(GroupArgs a, in
 }
 
 // Columns of the matrix: each count becomes the workflow's futures in earlier
-// tiles; a.key[1] receives the workflows' totals.  Thread (segment, column).
+// tiles; a.key[1] receives the workflows' totals.  Thread (segment, column): the
+// segments of one wave are scanned by shuffles, the waves' sums in order.
 // (Scanning the totals here too, by look-back over the workgroups, took as much
 // more here as it saved in every placing tile.)
-__global__ __launch_bounds__(kGroupWCols* kGroupWSegs) void k_groupw_scan(GroupArgs a, int64_t tiles) {
-  __shared__ uint32_t s_sum[kGroupWSegs][kGroupWCols];
+template <int kCols>
+__global__ __launch_bounds__(kGroupWScan) void k_groupw_scan(GroupArgs a, int64_t tiles) {
+  constexpr int kSegs = kGroupWScan / kCols, kWaves = kGroupWScan / kWave;
+  __shared__ uint32_t s_sum[kWaves][kCols];
   if (a.ctrl->status) return;
   const int W = int(a.p.W);
-  const int col = threadIdx.x % kGroupWCols, seg = threadIdx.x / kGroupWCols;
-  const int w = blockIdx.x * kGroupWCols + col;
+  const int col = threadIdx.x % kCols, seg = threadIdx.x / kCols, wv = threadIdx.x / kWave, ln = lane_id();
+  const int w = blockIdx.x * kCols + col;
   uint32_t carry = 0;
-  for (int64_t t0 = 0; t0 < tiles; t0 += kGroupWSegs * kGroupWPer) {
+  for (int64_t t0 = 0; t0 < tiles; t0 += kSegs * kGroupWPer) {
     uint32_t c[kGroupWPer], sum = 0;
 #pragma unroll
     for (int u = 0; u < kGroupWPer; ++u) {
@@ -1367,13 +1273,19 @@ __global__ __launch_bounds__(kGroupWCols* kGroupWSegs) void k_groupw_scan(GroupA
     }
 #pragma unroll
     for (int u = 0; u < kGroupWPer; ++u) sum += c[u];
-    s_sum[seg][col] = sum;
-    __syncthreads();
-    uint32_t run = carry;
+    uint32_t inc = sum;
 #pragma unroll
-    for (int q = 0; q < kGroupWSegs; ++q) {
+    for (int d = kCols; d < kWave; d <<= 1) {
+      const uint32_t y = __shfl_up(inc, d, kWave);
+      if (ln >= d) inc += y;
+    }
+    if (ln >= kWave - kCols) s_sum[wv][col] = inc;
+    __syncthreads();
+    uint32_t run = carry + inc - sum;
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) {
       const uint32_t x = s_sum[q][col];
-      run += q < seg ? x : 0u;
+      run += q < wv ? x : 0u;
       carry += x;
     }
 #pragma unroll
@@ -1629,25 +1541,11 @@ hipError_t launch_slack_sort(hipStream_t s, const SortArgs& a, int first_pass, i
 }
 
 bool group_places_first(const GroupArgs& a) {
-  return a.npass == 1 || groupw_tile(a.p.N, a.p.W, a.cap_n) != 0;
+  return groupw_tile(a.p.N, a.p.W, a.cap_n) != 0;
 }
 
 hipError_t launch_group(hipStream_t s, const GroupArgs& a, void (*mark)(void*, const char*),
                         void* ctx) {
-  const int64_t ntiles = (a.p.N + kSortTile - 1) / kSortTile;
-  if (a.npass == 1 && int64_t(kRadixBuckets) * ntiles <= a.cap_n) {  // at most 256 workflows
-    mark(ctx, "group_count");
-    hipLaunchKernelGGL(k_group1_count, dim3(ntiles), dim3(kSortThreads), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    mark(ctx, "group_scan");
-    hipLaunchKernelGGL(k_group1_scan, dim3(kRadixBuckets), dim3(kSortThreads), 0, s, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    mark(ctx, "group_place");
-    hipLaunchKernelGGL(k_group1_place, dim3(ntiles), dim3(kSortThreads), 0, s, a);
-    return hipGetLastError();
-  }
   if (const int64_t tile = groupw_tile(a.p.N, a.p.W, a.cap_n)) {
     const int64_t tiles = (a.p.N + tile - 1) / tile;
     const size_t lds = 4 * size_t((a.p.W + 3) & ~int64_t(3));
@@ -1658,8 +1556,12 @@ hipError_t launch_group(hipStream_t s, const GroupArgs& a, void (*mark)(void*, c
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     mark(ctx, "group_scan");
-    hipLaunchKernelGGL(k_groupw_scan, dim3(unsigned((a.p.W + kGroupWCols - 1) / kGroupWCols)),
-                       dim3(kGroupWCols * kGroupWSegs), 0, s, a, tiles);
+    if (a.p.W <= kRadixBuckets)
+      hipLaunchKernelGGL(k_groupw_scan<kGroupWFewCols>, dim3(unsigned((a.p.W + kGroupWFewCols - 1) / kGroupWFewCols)),
+                         dim3(kGroupWScan), 0, s, a, tiles);
+    else
+      hipLaunchKernelGGL(k_groupw_scan<kGroupWCols>, dim3(unsigned((a.p.W + kGroupWCols - 1) / kGroupWCols)),
+                         dim3(kGroupWScan), 0, s, a, tiles);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     mark(ctx, "group_place");

@@ -189,11 +189,11 @@ def test_wave_sweep_orders(policy, n, heavy):  # noqa: F811
 
 # ---------------------------------------------------------------- grouping by workflow
 
-@pytest.mark.parametrize("W,n", [(256, 9), (257, 9), (1023, 3), (1024, 5), (2048, 1), (2049, 2), (4097, 3),
+@pytest.mark.parametrize("W,n", [(1, 5000), (3, 700), (255, 30), (256, 9), (257, 9), (1023, 3), (1024, 5), (2048, 1), (2049, 2), (4097, 3),
                                  (16_384, 2), (16_385, 2), (300, 700)])
 def test_grouping_by_many_workflows(policy, W, n):  # noqa: F811
     """Ids of W workflows in random order, around the counts at which the
-    grouping changes (256 and 16,384 workflows) and its tile grows (2,048, 4,096
+    grouping changes (256 and 16,384 workflows, and few of them) and its tile grows (2,048, 4,096
     ...), with workflows left empty and one larger than the others."""
     rng = np.random.default_rng(W + n)
     p = _chained(W, n, W, False)
