@@ -727,6 +727,11 @@ static_assert(kBinSub == 1 << kBinSubLog && kBinSub % kBinBigThreads == 0, "sub-
 // key (children created alike) a bin's few networks of 33 to 64 entries cost more
 // than the whole rest (a store tick 200 -> 240 us); counted, 203 us.
 constexpr int kBinRun = 128;
+// The lowest and highest bin (outliers far from the other keys) count again on the
+// log-linear scale from here on: another count is cheaper than 33 to 128 mates
+// per future, and one slow bin is the kernel's end (1,024 bins, 1M ready futures:
+// 27.8 -> 24.2 us, together with tie-breaking compiled out where there is none).
+constexpr int kBinEdgeRun = 32;
 constexpr int kBinCrowdMax = kBinBigCap / (kBinRun + 1) + 1;  // crowded sub-buckets a bin can hold
 
 template <int NW>
@@ -836,14 +841,15 @@ __device__ void bin_bitonic(int64_t* k, int32_t* p, uint16_t* r, int32_t* w, int
   }
 }
 
-// Sorts bin b (n records, n <= LC) with T threads and writes it out.
+// Sorts bin b (n records, n <= LC) with T threads and writes it out; tw: the
+// workflows that break ties of the key before the position, or null.
 template <int T, int LC>
-__device__ void bin_sort_one(const SortArgs& a, const BucketArgs& bk, int b, int n, const BinLds<T / kWave>& L) {
+__device__ void bin_sort_one(const SortArgs& a, const BucketArgs& bk, int b, int n, const BinLds<T / kWave>& L,
+                             const int32_t* tw) {
   constexpr int kBinThreads = T;
   constexpr int kBinWaves = T / kWave;
   constexpr int kBinJ = (LC + T - 1) / T;  // items per lane
   const int cap = bk.cap;
-  const int32_t* tw = a.tie_wf;
   int64_t* s_key = L.key;
   int32_t* s_pos = L.pos;
   uint16_t* s_rec = L.rec;
@@ -925,7 +931,7 @@ __device__ void bin_sort_one(const SortArgs& a, const BucketArgs& bk, int b, int
     // the lowest or highest bin with a crowded sub-bucket counts again on
     // the log-linear scale
     bool crowded = false;
-    for (int i = tid; i < kBinSub; i += kBinThreads) crowded |= F->sub[i] > uint32_t(kBinRun);
+    for (int i = tid; i < kBinSub; i += kBinThreads) crowded |= F->sub[i] > uint32_t(kBinEdgeRun);
     if (!__syncthreads_or(crowded ? 1 : 0)) break;
     smode = b == 0 ? 1 : 2;
     sbase = b == 0 ? bk.split[0] - 1 : bk.split[bk.nb - 2];
@@ -1040,11 +1046,11 @@ __device__ void bin_sort_one(const SortArgs& a, const BucketArgs& bk, int b, int
 // k_bin_sort_big.  Workgroup 0 settles and publishes the status and range,
 // and the size of the largest bin (in max_bucket), from which the host plans
 // the next pass's bin capacity.
-template <int T>
+template <int T, bool kTie>
 __global__ __launch_bounds__(T) void k_bin_sort(SortArgs a, BucketArgs bk) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int NW = T / kWave;
-  const BinLds<NW> L = carve_bin<NW>(smem, kBinCap, a.tie_wf != nullptr);
+  const BinLds<NW> L = carve_bin<NW>(smem, kBinCap, kTie);
   const int b = blockIdx.x;
   if (b == 0) {
     __shared__ uint32_t s_mx[NW];
@@ -1078,7 +1084,7 @@ __global__ __launch_bounds__(T) void k_bin_sort(SortArgs a, BucketArgs bk) {
   const uint32_t nraw = bk.cnt[b];
   const int n = int(nraw < uint32_t(bk.cap) ? nraw : uint32_t(bk.cap));
   if (n > kBinCap) return;
-  bin_sort_one<T, kBinCap>(a, bk, b, n, L);
+  bin_sort_one<T, kBinCap>(a, bk, b, n, L, kTie ? a.tie_wf : nullptr);
 }
 
 // The bins of more than kBinCap records: every workgroup lists them in bin
@@ -1107,7 +1113,7 @@ __global__ __launch_bounds__(kBinBigThreads) void k_bin_sort_big(SortArgs a, Buc
   }
   for (int k = int(blockIdx.x); k < nbig; k += int(gridDim.x)) {
     const int b = s_big[k];
-    bin_sort_one<kBinBigThreads, kBinBigCap>(a, bk, b, int(bk.cnt[b]), L);
+    bin_sort_one<kBinBigThreads, kBinBigCap>(a, bk, b, int(bk.cnt[b]), L, a.tie_wf);
     __syncthreads();
   }
 }
@@ -1481,12 +1487,15 @@ hipError_t launch_bucket_sort(hipStream_t s, const SortArgs& a, const BucketArgs
 
 hipError_t launch_bin_sort(hipStream_t s, const SortArgs& a, const BucketArgs& bk) {
   const bool tie = a.tie_wf != nullptr;
-  if (tie || bk.nb > kBinNarrow)
-    hipLaunchKernelGGL(k_bin_sort<kBinWideThreads>, dim3(bk.nb), dim3(kBinWideThreads),
-                       bin_lds_bytes<kBinWideThreads / kWave>(kBinCap, tie), s, a, bk);
+  if (tie)
+    hipLaunchKernelGGL((k_bin_sort<kBinWideThreads, true>), dim3(bk.nb), dim3(kBinWideThreads),
+                       bin_lds_bytes<kBinWideThreads / kWave>(kBinCap, true), s, a, bk);
+  else if (bk.nb > kBinNarrow)
+    hipLaunchKernelGGL((k_bin_sort<kBinWideThreads, false>), dim3(bk.nb), dim3(kBinWideThreads),
+                       bin_lds_bytes<kBinWideThreads / kWave>(kBinCap, false), s, a, bk);
   else
-    hipLaunchKernelGGL(k_bin_sort<kBinThreads>, dim3(bk.nb), dim3(kBinThreads),
-                       bin_lds_bytes<kBinThreads / kWave>(kBinCap, tie), s, a, bk);
+    hipLaunchKernelGGL((k_bin_sort<kBinThreads, false>), dim3(bk.nb), dim3(kBinThreads),
+                       bin_lds_bytes<kBinThreads / kWave>(kBinCap, false), s, a, bk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || bk.cap <= kBinCap) return e;
   hipLaunchKernelGGL(k_bin_sort_big, dim3(kBinBigGroups), dim3(kBinBigThreads),
@@ -1499,11 +1508,15 @@ hipError_t prepare_sort_kernels() {
     const hipError_t eg = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, int(4 * kGroupWMax));
     if (eg != hipSuccess) return eg;
   }
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bin_sort<kBinThreads>),
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bin_sort<kBinThreads, false>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     int(bin_lds_bytes<kBinThreads / kWave>(kBinCap, true)));
+                                     int(bin_lds_bytes<kBinThreads / kWave>(kBinCap, false)));
   if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bin_sort<kBinWideThreads>),
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bin_sort<kBinWideThreads, false>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize,
+                          int(bin_lds_bytes<kBinWideThreads / kWave>(kBinCap, false)));
+  if (e != hipSuccess) return e;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bin_sort<kBinWideThreads, true>),
                           hipFuncAttributeMaxDynamicSharedMemorySize,
                           int(bin_lds_bytes<kBinWideThreads / kWave>(kBinCap, true)));
   if (e != hipSuccess) return e;
