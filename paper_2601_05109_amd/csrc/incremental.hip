@@ -13,7 +13,7 @@
 //   1. closure: from every seed, its dependencies are marked (one bit per
 //      future) and visited in turn;
 //   2. scan (every future, O(N + E)): readiness (not done, every dependency
-//      done) into a list of ready futures; for a closure member, one count per
+//      done) as one bit per future; for a closure member, one count per
 //      dependency (its consumers inside the closure); for a future outside
 //      the closure, its unchanged rem pushed to each dependency inside the
 //      closure (max);
