@@ -1082,11 +1082,16 @@ int nalar::policy_pass_incremental(nalar_policy* h, const nalar_problem* p, nala
   ia.host = h->host;
   // rounds with a launch of their own: as deep as the last pass had work (work
   // that comes deeper is done by the tail's one workgroup, and raises the next
-  // plan); an empty round costs a launch, 4 us
-  e = launch_inc_closure(s, ia, h->cus, 1 + int(st.rounds & 0xFFu), Timer::cb, &tm);
+  // plan); an empty round costs a launch, 4 us.  A large delta gets them all: a
+  // few hundred thousand seeds leave thousands of futures to the rounds after the
+  // first, which one workgroup takes far longer over than the launches cost.
+  const bool many = st.n_log + (N - st.n_prev) > kIncManySeeds;
+  const int close_rounds = many ? kIncRounds : 1 + int(st.rounds & 0xFFu);
+  const int sweep_rounds = many ? kIncRounds : 1 + int(st.rounds >> 8);
+  e = launch_inc_closure(s, ia, h->cus, close_rounds, Timer::cb, &tm);
   if (e != hipSuccess) return hip_fail(h, e, "inc_closure");
   NALAR_LAUNCH("inc_scan", launch_inc_scan(s, ia, h->cus));
-  e = launch_inc_sweep(s, ia, h->cus, 1 + int(st.rounds >> 8), Timer::cb, &tm);
+  e = launch_inc_sweep(s, ia, h->cus, sweep_rounds, Timer::cb, &tm);
   if (e != hipSuccess) return hip_fail(h, e, "inc_sweep");
   __atomic_store_n(&h->host->inc_rounds, kIncRoundsAll, __ATOMIC_RELEASE);
   NALAR_LAUNCH("inc_ready", launch_inc_ready(s, ia, h->cus));
