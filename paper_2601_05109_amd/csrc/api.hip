@@ -1084,7 +1084,8 @@ int nalar::policy_pass_incremental(nalar_policy* h, const nalar_problem* p, nala
   // that comes deeper is done by the tail's one workgroup, and raises the next
   // plan); an empty round costs a launch, 4 us.  A large delta gets them all: a
   // few hundred thousand seeds leave thousands of futures to the rounds after the
-  // first, which one workgroup takes far longer over than the launches cost.
+  // first, which one workgroup takes far longer over than the launches cost (325K
+  // seeds over 12.4M futures: 1,166 us, so 787).
   const bool many = st.n_log + (N - st.n_prev) > kIncManySeeds;
   const int close_rounds = many ? kIncRounds : 1 + int(st.rounds & 0xFFu);
   const int sweep_rounds = many ? kIncRounds : 1 + int(st.rounds >> 8);
