@@ -12,7 +12,9 @@
 //                the position of its only dependency, its id); a tile of ids
 //                writes runs of neighbouring positions, which the L2 joins;
 //   k_sweep_rec  by position: one workgroup per workflow, chunks of positions
-//                from the last to the first, rem written by position;
+//                from the last to the first, rem written by position; it also
+//                checks the dependencies of futures with more than kRecLight,
+//                whose lists it reads anyway, and decides their readiness;
 // and the ready kernel of the incremental pass (by id again) brings rem into the
 // caller's order while it keys, routes and bins the ready futures.
 //
@@ -20,12 +22,18 @@
 // pass is then done again by the block sweep, and the host leaves this path alone
 // for a while.
 //
-// Per future k_rec moves about 45 bytes (6.6M: 90 us, 3.3 TB/s, with one line
-// written per run of records) and k_sweep_rec 24 (78 us: 26 chunks of about 3 us,
+// Per future k_rec moves about 45 bytes (6.6M: 84 us, 3.5 TB/s, with one line
+// written per run of records) and k_sweep_rec 24 (83 us: 26 chunks of about 3 us,
 // three to five barriers and LDS trips each).  The whole pass over 6.6M futures of
-// 256 workflows went from 607 to 434 us: the block sweep took 424 us of it, these
-// two and the ready kernel take 278, and the bin sort 38 for 58, its futures
+// 256 workflows went from 607 to 430 us: the block sweep took 424 us of it, these
+// two and the ready kernel take 276, and the bin sort 38 for 58, its futures
 // having been appended a workgroup's worth at a time.
+//
+// The fan-ins of sessions started together are created together: with their
+// lists taken where their ids lie, in k_rec, one workgroup read 64 of them one
+// after another and single threads the rest (1.05M futures of 256 map/reduce
+// sessions in creation order: k_rec 4,600 us, now 17, the pass 4,734, now 162; the
+// block sweep's pass 181).
 #include "internal.hpp"
 
 namespace nalar {
@@ -35,9 +43,8 @@ namespace {
 constexpr int kRecThreads = 256;
 constexpr int kRecPer = 8;                       // futures per thread, kRecThreads apart
 constexpr int kRecTile = kRecThreads * kRecPer;
-constexpr int kRecLight = 32;                    // more dependencies: the workgroup together
-constexpr int kRecList = 64;                     // futures of many dependencies it lists
-constexpr int kRecWaves = kRecThreads / kWave;
+constexpr int kRecLight = 32;                    // more dependencies: left to the sweep's workgroups
+constexpr int kRecList = 64;                     // such futures a chunk of the sweep lists
 
 // A record's third word: the position (inside the workflow) of the future's only
 // dependency, or one of these.
@@ -66,18 +73,19 @@ __device__ inline int32_t rec_dep(const RecArgs& a, bool in_range, int32_t q, in
   return lp;
 }
 
+// Not this path: the host does the pass again.
+__device__ inline void flag_unordered(Ctrl* c) {
+  st_relaxed_agent(&c->unordered, 1u);
+  st_relaxed_agent(&c->bucket_overflow, 1u);
+}
+
 __global__ __launch_bounds__(kRecThreads) void k_rec(RecArgs a) {
   if (a.ctrl->status) return;
-  __shared__ unsigned long long s_ready[kRecTile / kWave];
-  __shared__ int s_hn, s_blocked, s_up;
-  __shared__ int32_t s_h[kRecList];
+  __shared__ int s_up;
   const int64_t N = a.p.N;
   const int tid = threadIdx.x, wv = tid / kWave, ln = lane_id();
   const int64_t t0 = int64_t(blockIdx.x) * kRecTile;
-  if (tid == 0) {
-    s_hn = 0;
-    s_up = 0;
-  }
+  if (tid == 0) s_up = 0;
   __syncthreads();
   int32_t o0[kRecPer], o1[kRecPer], w[kRecPer], q[kRecPer], d0[kRecPer], dq[kRecPer], b[kRecPer], n[kRecPer];
   int64_t est[kRecPer];
@@ -114,68 +122,31 @@ __global__ __launch_bounds__(kRecThreads) void k_rec(RecArgs a) {
     const int32_t k = q[j] - b[j], nn = n[j] - b[j];
     bool ready = v < N && dn[j] == 0;
     int32_t one = kRecNone;
-    if (v < N && deg > 0) {
-      if (deg <= kRecLight) {
-        const int32_t lp = rec_dep(a, d0[j] >= 0 && int64_t(d0[j]) < N, dq[j], b[j], nn, k, up);
-        if (lp >= 0 && !dd[j]) ready = false;
-        one = deg == 1 ? lp : kRecMany;
-        for (int32_t e = o0[j] + 1; e < o1[j]; ++e) {
-          const int32_t d = a.p.dep_idx[e];
-          const bool ok = d >= 0 && int64_t(d) < N;
-          const int32_t x = rec_dep(a, ok, ok ? a.pos_of_node[d] : 0, b[j], nn, k, up);
-          if (x >= 0 && !done_of(a.done_bits, d)) ready = false;
-        }
-      } else {
-        one = kRecMany;
-        const int at = atomicAdd(&s_hn, 1);
-        if (at < kRecList) {
-          s_h[at] = int32_t(v - t0);
-          ready = false;  // decided below
-        } else {  // the list is full: this thread alone
-          for (int32_t e = o0[j]; e < o1[j]; ++e) {
-            const int32_t d = a.p.dep_idx[e];
-            const bool ok = d >= 0 && int64_t(d) < N;
-            const int32_t x = rec_dep(a, ok, ok ? a.pos_of_node[d] : 0, b[j], nn, k, up);
-            if (x >= 0 && !done_of(a.done_bits, d)) ready = false;
-          }
-        }
+    if (v < N && deg > kRecLight) {
+      one = kRecMany;
+      ready = false;  // the sweep decides
+    } else if (v < N && deg > 0) {
+      const int32_t lp = rec_dep(a, d0[j] >= 0 && int64_t(d0[j]) < N, dq[j], b[j], nn, k, up);
+      if (lp >= 0 && !dd[j]) ready = false;
+      one = deg == 1 ? lp : kRecMany;
+      for (int32_t e = o0[j] + 1; e < o1[j]; ++e) {
+        const int32_t d = a.p.dep_idx[e];
+        const bool ok = d >= 0 && int64_t(d) < N;
+        const int32_t x = rec_dep(a, ok, ok ? a.pos_of_node[d] : 0, b[j], nn, k, up);
+        if (x >= 0 && !done_of(a.done_bits, d)) ready = false;
       }
     }
     const uint64_t m = ballot(ready);
-    if (ln == 0) s_ready[j * kRecWaves + wv] = m;
+    const int64_t v0 = t0 + j * kRecThreads + wv * kWave;
+    if (ln == 0 && v0 < N) a.rbits[v0 / kWave] = m;
     if (v < N) {
       const int64_t e = dn[j] ? 0 : est[j];
       a.rec[q[j]] = make_uint4(uint32_t(uint64_t(e)), uint32_t(uint64_t(e) >> 32), uint32_t(one), uint32_t(v));
     }
   }
-  __syncthreads();
-  const int nh = s_hn < kRecList ? s_hn : kRecList;
-  for (int h = 0; h < nh; ++h) {  // the workgroup together
-    const int at = s_h[h];
-    const int64_t v = t0 + at;
-    if (tid == 0) s_blocked = 0;
-    __syncthreads();
-    const int32_t hw = a.p.wf[v], hb = a.wf_off[hw], hn = a.wf_off[hw + 1] - hb, hk = a.pos_of_node[v] - hb;
-    const int32_t e1 = a.p.dep_off[v + 1];
-    bool blocked = false;
-    for (int32_t e = a.p.dep_off[v] + tid; e < e1; e += kRecThreads) {
-      const int32_t d = a.p.dep_idx[e];
-      const bool ok = d >= 0 && int64_t(d) < N;
-      const int32_t x = rec_dep(a, ok, ok ? a.pos_of_node[d] : 0, hb, hn, hk, up);
-      if (x >= 0) blocked |= !done_of(a.done_bits, d);
-    }
-    if (blocked) s_blocked = 1;
-    __syncthreads();
-    if (tid == 0 && a.p.done[v] == 0 && s_blocked == 0) s_ready[at / kWave] |= 1ull << (at % kWave);
-  }
   if (up) s_up = 1;
   __syncthreads();
-  for (int i = tid; i < kRecTile / kWave; i += kRecThreads)
-    if (t0 + int64_t(i) * kWave < N) a.rbits[t0 / kWave + i] = s_ready[i];
-  if (tid == 0 && s_up) {  // not this path: the host does the pass again
-    st_relaxed_agent(&a.ctrl->unordered, 1u);
-    st_relaxed_agent(&a.ctrl->bucket_overflow, 1u);
-  }
+  if (tid == 0 && s_up) flag_unordered(a.ctrl);
 }
 
 // ------------------------------------------------------------------- sweep
@@ -212,6 +183,7 @@ __global__ __launch_bounds__(kRecT) void k_sweep_rec(RecArgs a, int win) {
   __shared__ int32_t s_hk[kRecList], s_hv[kRecList];  // listed futures of many dependencies: position, id
   __shared__ int64_t s_hr[kRecList];                  // their rem so far
   __shared__ int s_hg[kRecList];                      // grown this round
+  __shared__ int s_hb[kRecList];                      // some dependency is open
   __shared__ int s_any[3];                            // some push inside the chunk, by round
   const int tid = threadIdx.x;
   Ctrl* ctrl = a.ctrl;
@@ -219,6 +191,7 @@ __global__ __launch_bounds__(kRecT) void k_sweep_rec(RecArgs a, int win) {
   __syncthreads();
   if (s_stop) return;
   const int64_t N = a.p.N;
+  bool up = false;
 
   for (int64_t w = blockIdx.x; w < a.p.W; w += gridDim.x) {
     const int32_t b = a.wf_off[w];
@@ -232,6 +205,20 @@ __global__ __launch_bounds__(kRecT) void k_sweep_rec(RecArgs a, int win) {
       const int32_t d = a.p.dep_idx[e];
       const int32_t lp = d >= 0 && int64_t(d) < N ? a.pos_of_node[d] - b : -1;
       return lp < n ? lp : -1;
+    };
+    // the same, checked, for the future of many dependencies at position hk
+    auto check_pos = [&](int32_t e, int32_t hk, bool& blocked) -> int32_t {
+      const int32_t d = a.p.dep_idx[e];
+      const bool ok = d >= 0 && int64_t(d) < N;
+      const int32_t q = a.pos_of_node[ok ? d : 0];
+      const bool dd = done_of(a.done_bits, ok ? d : 0);
+      const int32_t lp = rec_dep(a, ok, q, b, n, hk, up);
+      blocked |= lp >= 0 && !dd;
+      return lp;
+    };
+    auto set_ready = [&](int32_t hv) {  // no dependency of hv is open
+      if (!done_of(a.done_bits, hv))
+        atomicOr(reinterpret_cast<unsigned long long*>(&a.rbits[uint32_t(hv) / kWave]), 1ull << (uint32_t(hv) % kWave));
     };
     bool overflow = false;
     // (behind the barrier the last workflow ended with)
@@ -276,12 +263,13 @@ __global__ __launch_bounds__(kRecT) void k_sweep_rec(RecArgs a, int win) {
         if (slot < kRecList) {
           s_hk[slot] = k;
           s_hv[slot] = v;
+          s_hb[slot] = 0;
         } else {
           slot = -1;  // the list is full: its thread pushes alone
         }
       }
       lds_barrier();
-      const int nh = s_hn < kRecList ? s_hn : kRecList;
+      const int nh = __builtin_amdgcn_readfirstlane(s_hn < kRecList ? s_hn : kRecList);
       // 1: inside the chunk
       int64_t r = -1;
       for (int round = 0;; ++round) {
@@ -309,7 +297,7 @@ __global__ __launch_bounds__(kRecT) void k_sweep_rec(RecArgs a, int win) {
           } else if (one == kRecMany) {
             for (int32_t e = o0; e < o1; ++e) {
               const int32_t lp = dep_pos(e);
-              if (lp >= c0 && lp != k) {
+              if (lp >= c0 && lp < k) {
                 lds_max(&mx[lp - c0], r);
                 pushed = true;
               }
@@ -324,7 +312,7 @@ __global__ __launch_bounds__(kRecT) void k_sweep_rec(RecArgs a, int win) {
             const int32_t hv = s_hv[h], hk = s_hk[h], e1 = a.p.dep_off[hv + 1];
             for (int32_t e = a.p.dep_off[hv] + tid; e < e1; e += T) {
               const int32_t lp = dep_pos(e);
-              if (lp >= c0 && lp != hk) {
+              if (lp >= c0 && lp < hk) {
                 lds_max(&mx[lp - c0], hr);
                 pushed = true;
               }
@@ -361,24 +349,35 @@ __global__ __launch_bounds__(kRecT) void k_sweep_rec(RecArgs a, int win) {
       if (own) rem[k] = r;
       push_out(one, r);
       {
-        const bool alone = one == kRecMany && slot < 0;
-        for (int32_t e = o0; ballot(alone && e < o1) != 0; ++e) push_out(alone && e < o1 ? dep_pos(e) : -1, r);
+        const bool alone = one == kRecMany && slot < 0, open = alone && o1 - o0 > kRecLight;
+        const int32_t e1 = open ? o0 : o1;
+        for (int32_t e = o0; ballot(alone && e < e1) != 0; ++e) push_out(alone && e < e1 ? dep_pos(e) : -1, r);
+        if (ballot(open) != 0) {
+          bool blocked = false;
+          for (int32_t e = o0; ballot(open && e < o1) != 0; ++e)
+            push_out(open && e < o1 ? check_pos(e, k, blocked) : -1, r);
+          if (open && !blocked) set_ready(v);
+        }
       }
       for (int h = 0; h < nh; ++h) {
         const int64_t hr = s_hr[h];
-        const int32_t hv = s_hv[h], e1 = a.p.dep_off[hv + 1];
+        const int32_t hv = s_hv[h], hk = s_hk[h], e1 = a.p.dep_off[hv + 1];
+        bool blocked = false;
         for (int32_t e0 = a.p.dep_off[hv]; e0 < e1; e0 += T) {
           const int32_t e = e0 + tid;
-          push_out(e < e1 ? dep_pos(e) : -1, hr);
+          push_out(e < e1 ? check_pos(e, hk, blocked) : -1, hr);
         }
+        if (blocked) s_hb[h] = 1;
       }
       cur = next;
       next = after;
       far = far1;
       lds_barrier();
+      if (nh > 0 && tid < nh && s_hb[tid] == 0) set_ready(s_hv[tid]);
     }
     if (overflow) flag_sweep(ctrl, kStRange);
   }
+  if (ballot(up) != 0 && lane_id() == 0 && ld_relaxed_agent(&ctrl->unordered) == 0) flag_unordered(ctrl);
 }
 
 size_t sweep_rec_lds(int win) { return 8 * size_t(kRecT) * size_t(win); }

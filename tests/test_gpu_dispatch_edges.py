@@ -323,3 +323,93 @@ def test_record_sweep(W, n):
             R = out.n_ready
             assert R == o.n_ready and np.array_equal(out.order[:R].cpu().numpy(), o.order)
             assert np.array_equal(out.cost[:R].cpu().numpy(), o.cost)
+
+
+def _rooted(W, n, deps_of, seed):
+    """W workflows of n futures: a finished root, its children, and for each
+    (i, parents) of deps_of(w, rng) a future i of many dependencies; ids by creation,
+    the workflows interleaved (position i of every workflow before i + 1)."""
+    rng = np.random.default_rng(seed)
+    lists = [[[]] + [[0]] * (n - 1) for _ in range(W)]
+    for w in range(W):
+        for i, par in deps_of(w, rng):
+            lists[w][i] = [int(q) for q in par]
+    done = np.zeros((W, n), np.uint8)
+    done[:, 0] = 1
+    done[::3, 1:] = 1                      # every third workflow: only its futures of many dependencies are left
+    for w in range(W):
+        for i, par in enumerate(lists[w]):
+            if len(par) > 1:
+                done[w, i] = 0
+    counts = np.array([len(par) for ls in lists for par in ls], np.int64)
+    flat = np.array([w * n + q for w, ls in enumerate(lists) for par in ls for q in par], np.int64)
+    N, M, K, now = W * n, 40, 6, 5_000
+    p = wl.Problem(f"rooted-{W}x{n}", now, 150_000, np.repeat(np.arange(W, dtype=np.int32), n),
+                   rng.integers(0, K, N).astype(np.int32), rng.integers(0, 10**6, N).astype(np.int64), done.reshape(-1),
+                   np.where(rng.random(N) < 0.5, rng.integers(0, M, N), -1).astype(np.int32),
+                   np.concatenate([[0], np.cumsum(counts)]).astype(np.int32), flat.astype(np.int32),
+                   (now + rng.integers(0, 10**7, W)).astype(np.int64), (np.arange(M) % K).astype(np.int32),
+                   rng.integers(0, 10**6, M).astype(np.int64), rng.integers(300, 3000, M).astype(np.int32),
+                   wf_contiguous=True)
+    local, w = np.tile(np.arange(n), W), np.repeat(np.arange(W), n)
+    return wl.relabel(p, local * W + w)
+
+
+def test_record_sweep_fan_ins_created_together():
+    """One fan-in over a whole workflow each, all created last (map/reduce sessions
+    started together): the fan-ins' ids lie side by side, and whatever takes their
+    dependencies must spread over the workflows' workgroups.  Taken by the one
+    workgroup that holds their ids it was 4.6 ms at 256 workflows of 4,098 futures,
+    0.03 ms without; the bound leaves a factor of ten to either side."""
+    W, n = 256, 2050
+    p = _rooted(W, n, lambda w, rng: [(n - 1, range(1, n - 1))], 1)
+    with nalar.Policy() as pol:
+        pol.set_timing(True)
+        for rep in range(3):
+            check(pol, p, f"fan-ins pass {rep}")
+            ms = dict(pol.timing())
+            say(f"  {ms}")
+            if rep:
+                assert ms["records"] < 0.3
+
+
+@pytest.mark.parametrize("n_many,deg", [(1, 33), (1, 1200), (64, 33), (65, 40), (700, 34)])
+def test_record_sweep_many_dependencies(n_many, deg):
+    """Futures of more than 32 dependencies, one to 700 in a workflow (a chunk of
+    the sweep lists 64 of them, the others push alone): ready and blocked ones, and
+    the problems only they have: a dependency on another workflow, on itself, at a
+    higher id (the block sweep then does the pass) and in a cycle."""
+    W, n = 100, 2100
+
+    def deps_of(w, rng):
+        return [(i, rng.choice(np.arange(1, n - n_many), deg, replace=False)) for i in range(n - n_many, n)]
+
+    p = _rooted(W, n, deps_of, n_many + deg)
+    deg_of = np.diff(p.dep_off)
+    many = np.flatnonzero(deg_of > 32)
+    assert many.size == W * n_many
+    ref = oracle.run(p)
+    assert 0 < np.isin(many, ref.order).sum() < many.size    # some ready, some blocked
+    v = int(many[many.size // 2])
+    other = int(np.flatnonzero(p.wf != p.wf[v])[7])
+    later = int(p.n_nodes - W + p.wf[v])                     # the last future of v's workflow
+    cases = [("foreign", v, other, oracle.EINVAL), ("itself", v, v, oracle.ECYCLE)]
+    if later != v:
+        cases.append(("higher", v, later, oracle.OK))
+    with nalar.Policy() as pol:
+        pol.set_timing(True)
+        for rep, policy in enumerate((0, 0, nalar.NALAR_ORDER_LPT)):
+            check(pol, p, f"many {n_many}x{deg} pass {rep}", policy=policy)
+            assert rep == 0 or "records" in [k for k, _ in pol.timing()]
+        for name, at, dep, status in cases:
+            q = p.copy()
+            q.dep_idx[q.dep_off[at] + deg // 2] = dep
+            assert oracle.run(q).status == status
+            check(pol, q, f"many {n_many}x{deg} {name}")
+            for rep in range(3):
+                check(pol, p, f"many {n_many}x{deg} after {name} {rep}")
+        if later != v:                                       # higher, and the other way round: a cycle
+            q.dep_idx[q.dep_off[later] + 1] = v
+            assert oracle.run(q).status == oracle.ECYCLE
+            check(pol, q, f"many {n_many}x{deg} cycle")
+            check(pol, p, f"many {n_many}x{deg} after the cycle")
