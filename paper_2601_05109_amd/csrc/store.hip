@@ -55,6 +55,7 @@ struct nalar_store {
   int32_t* rheavy = nullptr;    // [capH]
   uint32_t* hv_n = nullptr;     // their number (device memory; the appends count)
   int64_t capH = 0;
+  bool hv_stale = false;        // a malformed append may be missing from hv
   IncCtrl* ic = nullptr;
   uint32_t rounds = kIncRoundsAll;  // depth of the last incremental pass (the next one's launch plan)
   int32_t* log = nullptr;       // ids completed since the last pass
@@ -102,6 +103,19 @@ struct AppendArgs {
   int64_t hv_cap;
 };
 
+// Lists future v; false when the list is full.  The count stays at the entries
+// written (a full list's count only rises above its capacity for a moment, and
+// no entry is freed), so every counted entry is a stored future's id.
+__device__ inline bool list_heavy(int32_t* hv, uint32_t* hv_n, int64_t cap, int32_t v) {
+  const uint32_t at = atomicAdd(hv_n, 1u);
+  if (int64_t(at) < cap) {
+    hv[at] = v;
+    return true;
+  }
+  atomicSub(hv_n, 1u);
+  return false;
+}
+
 __global__ __launch_bounds__(kStoreThreads) void k_store_append(AppendArgs a) {
   bool b = false;
   const int64_t step = int64_t(gridDim.x) * kStoreThreads;
@@ -121,14 +135,21 @@ __global__ __launch_bounds__(kStoreThreads) void k_store_append(AppendArgs a) {
     // (the degree as stored: off[0] was written by the append before)
     const int64_t deg = int64_t(a.base) + x1 - (i == 0 ? int64_t(a.off[0]) : int64_t(a.base) + x0);
     if (deg > kIncHeavy) {
-      const uint32_t at = atomicAdd(a.hv_n, 1u);
-      if (int64_t(at) < a.hv_cap) a.hv[at] = a.id0 + int32_t(i);
-      else b = true;  // more than the edges allow: malformed offsets
+      // more than the edges allow: malformed offsets
+      b |= !list_heavy(a.hv, a.hv_n, a.hv_cap, a.id0 + int32_t(i));
     }
   }
   for (int64_t e = g0; e < a.n_edges; e += step) a.idx[e] = a.sidx[e];
   if (ballot(b) != 0 && lane_id() == 0)
     __hip_atomic_fetch_add(a.bad, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The list of futures with more than kIncHeavy dependencies made again from
+// validated offsets (a malformed append may have left futures out of it).
+__global__ __launch_bounds__(kStoreThreads) void k_store_heavy(const int32_t* off, int64_t N, int32_t* hv,
+                                                               uint32_t* hv_n, int64_t cap) {
+  for (int64_t i = int64_t(blockIdx.x) * kStoreThreads + threadIdx.x; i < N; i += int64_t(gridDim.x) * kStoreThreads)
+    if (off[i + 1] - off[i] > kIncHeavy) list_heavy(hv, hv_n, cap, int32_t(i));
 }
 
 // Completed ids: their done flags set, and the ids kept for the next pass (log).
@@ -452,6 +473,19 @@ int nalar_store_pass(nalar_store* st, int64_t now_us, int64_t migration_cost_us,
     }
   }
   const bool bad = bad_calls();
+  st->hv_stale |= bad;
+  if (rc == NALAR_OK && !bad && st->hv_stale && st->N > 0) {
+    // (a full pass: the bad call's had no rem to leave)
+    hipStream_t s = policy_stream(st->h);
+    hipError_t e = launch_inc_clear(s, st->hv_n, 1);
+    if (e == hipSuccess) {
+      hipLaunchKernelGGL(k_store_heavy, dim3(grid_for(st->N)), dim3(kStoreThreads), 0, s, st->dep_off, st->N, st->hv,
+                         st->hv_n, st->capH);
+      e = hipGetLastError();
+    }
+    if (e != hipSuccess) rc = store_fail(st, e, "store heavy list");
+    else st->hv_stale = false;
+  }
   st->rem_valid = rc == NALAR_OK && !bad;
   st->n_prev = st->N;
   st->W_prev = st->W;

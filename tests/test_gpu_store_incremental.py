@@ -356,3 +356,59 @@ def test_store_incremental_random_streams():
                 st.close()
     say(f"[gpu] random streams: {n_pass} passes, {n_inc} incremental")
     assert n_inc * 2 > n_pass, (n_inc, n_pass)
+
+
+def test_store_heavy_list_after_malformed_append():
+    """An append whose offsets promise more dependencies than it brings, made good by
+    the next append: the pass after it is EINVAL, and the passes after that see every
+    future of many dependencies.  1,100 such futures are more than the list of them
+    has room for at the malformed append (1,024), and fewer than it has after the
+    next one: an entry counted there but not written would be read as an id."""
+    n0, k, deg = 3000, 1100, 65
+    rng = np.random.default_rng(5)
+    now, M, K = 10_000, 12, 3
+    p = wl.Problem("independent", now, 150, np.zeros(n0, np.int32), rng.integers(0, K, n0).astype(np.int32),
+                   rng.integers(1, 500, n0), np.zeros(n0, np.uint8), np.full(n0, -1, np.int32),
+                   np.zeros(n0 + 1, np.int32), np.zeros(0, np.int32), np.array([now + 5000]),
+                   (np.arange(M) % K).astype(np.int32), rng.integers(0, 500, M), np.full(M, 1000, np.int32),
+                   wf_contiguous=True)
+    e0 = p.n_edges
+    extra = 10                                    # dependencies the malformed append brings
+    total = k * deg + 10                          # and those of both appends together
+    idx = rng.integers(0, 200, total).astype(np.int32)
+    t = k + 2                                     # the malformed append's futures and two more
+
+    def cat(a, b):
+        return np.concatenate([a, np.asarray(b, a.dtype)])
+
+    off = np.concatenate([deg * np.arange(1, k + 1), [k * deg + 5, total]]).astype(np.int32)
+    kinds, est = rng.integers(0, 3, t).astype(np.int32), rng.integers(1, 500, t).astype(np.int64)
+    zeros, none = np.zeros(t, np.uint8), np.full(t, -1, np.int32)
+    q = wl.Problem("malformed", p.now_us, p.migration_cost_us, cat(p.wf, np.zeros(t)), cat(p.type, kinds),
+                   cat(p.est_us, est), cat(p.done, zeros), cat(p.loc, none), cat(p.dep_off, e0 + off),
+                   cat(p.dep_idx, idx), p.deadline_us, p.inst_type, p.inst_load_us, p.inst_speed_permille)
+    with nalar.Policy() as pol, nalar.Store(pol) as st:
+        feed(st, p, 0, None)
+        g, _ = store_pass(pol, st, p)
+        assert_parity(g, oracle.run(p), "before")
+        wf = np.zeros(t, np.int32)
+        assert st.append(wf[:k], kinds[:k], est[:k], zeros[:k], none[:k],
+                         np.concatenate([[0], off[:k]]).astype(np.int32), idx[:extra]) == 0
+        assert st.append(wf[k:], kinds[k:], est[k:], zeros[k:], none[k:],
+                         np.concatenate([[0], off[k:] - extra]).astype(np.int32), idx[extra:]) == 0
+        g, _ = store_pass(pol, st, q)
+        assert g["status"] == nalar.NALAR_EINVAL
+        g, inc = store_pass(pol, st, q)
+        assert not inc
+        assert_parity(g, oracle.run(q), "the full pass after it")
+        prev = (q.n_nodes, q.done.copy())
+        for tick in range(4):                     # in the end every dependency is done
+            q = q.copy()
+            open_ids = np.flatnonzero(q.done[:200] == 0)
+            q.done[open_ids if tick == 3 else rng.choice(open_ids, open_ids.size // 2, replace=False)] = 1
+            prev = feed(st, q, *prev)
+            g, inc = store_pass(pol, st, q)
+            assert inc, st.last_fallback
+            ref = oracle.run(q)
+            assert_parity(g, ref, f"tick {tick}")
+        assert ref.n_ready == n0 - 200 + t
