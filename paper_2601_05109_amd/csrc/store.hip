@@ -315,10 +315,15 @@ int nalar_store_append(nalar_store* st, int64_t n_new, int64_t n_new_edges, cons
   }
   {  // room for every future of more than kIncHeavy dependencies
     const int64_t need_h = (E + n_new_edges) / (kIncHeavy + 1) + 1;
-    if (!st->hv_n) {
-      e = hipMalloc(&st->hv_n, sizeof(uint32_t));
-      if (e == hipSuccess) e = launch_inc_clear(s, st->hv_n, 1);
-      if (e != hipSuccess) return store_fail(st, e, "store grow");
+    if (!st->hv_n) {  // (kept only once its clearing is enqueued)
+      uint32_t* count = nullptr;
+      e = hipMalloc(&count, sizeof(uint32_t));
+      if (e == hipSuccess) e = launch_inc_clear(s, count, 1);
+      if (e != hipSuccess) {
+        if (count) (void)hipFree(count);
+        return store_fail(st, e, "store grow");
+      }
+      st->hv_n = count;
     }
     if (need_h > st->capH) {
       int64_t c0 = st->capH;
