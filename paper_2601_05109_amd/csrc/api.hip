@@ -1117,9 +1117,9 @@ int nalar::policy_pass_incremental(nalar_policy* h, const nalar_problem* p, nala
   __atomic_store_n(&h->host->max_bucket, 0u, __ATOMIC_RELAXED);
   __atomic_store_n(&h->host->split_nb, 0u, __ATOMIC_RELAXED);
   __atomic_store_n(&h->host->status, 0xFFFFFFFFu, __ATOMIC_RELEASE);
+  __atomic_store_n(&h->host->aux_status, 0u, __ATOMIC_RELEASE);  // (read below also when nothing is routed)
   NALAR_LAUNCH("sort_bin", launch_bin_sort(s, sa, bk));
   if ((policy & NALAR_ROUTE_GREEDY) && M > 0) {
-    __atomic_store_n(&h->host->aux_status, 0u, __ATOMIC_RELEASE);
     const GreedyArgs g = greedy_args(h, p, r, policy, ctrl, sa.passes_launched);
     NALAR_LAUNCH("route_greedy", launch_route_greedy(s, g));
   }

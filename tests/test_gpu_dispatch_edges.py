@@ -413,3 +413,25 @@ def test_record_sweep_many_dependencies(n_many, deg):
             assert oracle.run(q).status == oracle.ECYCLE
             check(pol, q, f"many {n_many}x{deg} cycle")
             check(pol, p, f"many {n_many}x{deg} after the cycle")
+
+
+def test_store_greedy_without_instances_after_a_load_overflow():
+    """A load overflow of one greedy pass is not reported by the next pass of the
+    handle that has nothing to route: an incremental store pass without instances."""
+    G = nalar.NALAR_ROUTE_GREEDY
+    p = _independent(500, 4, 3, 1).copy(loc=np.full(500, -1, np.int32), wf_contiguous=False)
+    none = {f: getattr(p, f)[:0].copy() for f in ("inst_type", "inst_load_us", "inst_speed_permille")}
+    p = p.copy(**none)
+    n = 5000
+    over = _one_type(1, np.array([1 << 60]), np.array([1]), np.full(n, (1 << 40) - 1, np.int64))
+    assert oracle.run(over, policy=G).status == oracle.ERANGE
+    with nalar.Policy() as pol, nalar.Store(pol) as st:
+        prev = feed(st, p, 0, None)
+        store_pass(pol, st, p, policy=G)
+        check(pol, over, "load overflow", policy=G)
+        p = p.copy()
+        p.done[:40] = 1
+        prev = feed(st, p, *prev)
+        g, inc = store_pass(pol, st, p, policy=G)
+        assert inc, st.last_fallback
+        assert_parity(g, oracle.run(p, policy=G), "without instances")
