@@ -516,6 +516,11 @@ class Store:
         return nalar_store_last_fallback(self.handle)
 
     def run_pass(self, out: "DeviceResult", now_us: int, migration_cost_us: int, policy: int = 0) -> int:
+        """One pass over the stored snapshot.  The store grows with every append,
+        and a pass writes the remaining path of every stored future: ValueError
+        when ``out.rem`` has fewer entries."""
+        if out.rem is not None and out.rem.numel() < self.n_nodes:
+            raise ValueError(f"out.rem holds {out.rem.numel()} futures, the store {self.n_nodes}")
         cr = out.c_struct()
         rc = nalar_store_pass(self.handle, now_us, migration_cost_us, policy, cr)
         out.n_ready = int(cr.n_ready) if rc == NALAR_OK else 0

@@ -150,3 +150,22 @@ def test_kernels_keep_their_registers(tmp_path):
     assert worst, "no kernel resource remarks"
     over = {k: v for k, v in worst.items() if v > 96}
     assert not over, f"kernels spilling to scratch: {over}"
+
+
+def test_store_pass_refuses_outputs_the_store_has_outgrown(monkeypatch):
+    """Appends grow a store past outputs allocated for it earlier; a pass over it
+    would write the remaining paths past their end."""
+    from paper_2601_05109_amd import nalar
+    passes = []
+    monkeypatch.setattr(nalar, "nalar_store_n_nodes", lambda h: 10)
+    monkeypatch.setattr(nalar, "nalar_store_pass", lambda *a: passes.append(a) or nalar.NALAR_OK)
+    st = object.__new__(nalar.Store)
+    st.handle = None
+    short = nalar.DeviceResult.alloc(9, device="cpu")
+    with pytest.raises(ValueError, match="9 futures, the store 10"):
+        st.run_pass(short, 0, 0)
+    assert not passes
+    for out in (nalar.DeviceResult.alloc(10, device="cpu"), nalar.DeviceResult.alloc(12, device="cpu"),
+                nalar.DeviceResult.alloc(9, device="cpu", rem=False)):
+        assert st.run_pass(out, 0, 0) == nalar.NALAR_OK
+    assert len(passes) == 3
