@@ -141,7 +141,8 @@ struct nalar_policy {
   bool bucket_relaxed = false;   // the last pass tried fewer buckets
   int split_nb = 0;              // bins the current splitters are for (0: none)
   int split_cur = 0;             // the splitter buffer the next pass reads
-  int rec_skip = 0;              // passes left before the record sweep is tried again
+  bool rec_ok = false;           // the record sweep may be taken: the last look at the ids' order found none wrong
+  int rec_skip = 0;              // passes left before the order is looked at again
   int rec_backoff = 1;
   int bin_skip = 0;              // passes left before bins are tried again
   int bin_backoff = 1;
@@ -737,10 +738,23 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
 
   // The record sweep (grouped.hip): a snapshot the library groups itself, of
   // workflows beyond the wave sweep, with bins planned; not where a testing flag
-  // asks for one of the block sweep's forms, and not for a while after a snapshot
-  // it could not take (ids not in topological order).
-  const bool rec = N > 0 && bk.bins && node_of_pos && !sh.wave_path && own_splitters && h->rec_skip == 0 &&
-                   !(h->flags & (NALAR_FORCE_GLOBAL_SWEEP | NALAR_FORCE_LEVEL_SWEEP));
+  // asks for one of the block sweep's forms, and only behind a pass whose probe
+  // found the ids in topological order.  The probe runs behind the block sweep,
+  // on a handle's first large pass and, while it finds them in another order, 1, 2, 4 ...
+  // 64 passes apart (20 us at 1.3M futures, 50 at 4.6M).
+  const bool rec_able = N > 0 && node_of_pos && !sh.wave_path && own_splitters && !p->wf_priority &&
+                        !(h->flags & (NALAR_FORCE_GLOBAL_SWEEP | NALAR_FORCE_LEVEL_SWEEP | NALAR_FORCE_TILED_SORT));
+  const bool rec = rec_able && bk.bins && h->rec_ok;
+  bool probe = rec_able && !h->rec_ok && (bk.bins || N >= kBinMinReady);
+  if (probe && h->rec_skip > 0) {
+    --h->rec_skip;
+    probe = false;
+  }
+  auto rec_back_off = [h]() {
+    h->rec_ok = false;
+    h->rec_skip = h->rec_backoff;
+    h->rec_backoff = h->rec_backoff < 64 ? 2 * h->rec_backoff : 64;
+  };
   SweepArgs sw{};
   BlockSweepArgs ba{};
   if (N > 0) {
@@ -795,6 +809,10 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
       NALAR_LAUNCH("ready", launch_inc_ready(s, ia, h->cus, true));
     } else {
       NALAR_LAUNCH("sweep", launch_sweep(s, sw, ba, sh));
+      if (probe) {
+        __atomic_store_n(&h->host->higher, 0u, __ATOMIC_RELEASE);
+        NALAR_LAUNCH("order_probe", launch_order_probe(s, pd, ctrl, h->host));
+      }
     }
     as.bcnt_clean[nxt] = true;  // the sweep cleared them for the next pass
   }
@@ -873,8 +891,7 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
       sa.node_of_pos = node_of_pos;  // the sweep below stages by position
       sa.tie_wf = nullptr;
       if (rec && __atomic_load_n(&h->host->unordered, __ATOMIC_ACQUIRE) != 0) {
-        h->rec_skip = h->rec_backoff;
-        h->rec_backoff = h->rec_backoff < 64 ? 2 * h->rec_backoff : 64;
+        rec_back_off();
       } else if (bk.bins) {  // a bin overflowed: new splitters come from the tiled sort; back off
         h->bin_max = 0;
         h->bin_skip = h->bin_backoff;
@@ -948,6 +965,10 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
   if (st & kStCycle) return fail(h, NALAR_ECYCLE, "dependency cycle");
   if (st & kStRange) return fail(h, NALAR_ERANGE, "remaining critical path exceeds 2^62 us");
   r->n_ready = __atomic_load_n(&h->host->n_ready, __ATOMIC_ACQUIRE);
+  if (probe) {
+    if (__atomic_load_n(&h->host->higher, __ATOMIC_ACQUIRE) != 0) rec_back_off();
+    else h->rec_ok = true;
+  }
   if (want_split || bk.bins) {  // splitters written for the next pass: read them from now on
     const uint32_t snb = __atomic_load_n(&h->host->split_nb, __ATOMIC_ACQUIRE);
     h->split_nb = int(snb);
@@ -1176,7 +1197,6 @@ int nalar_policy_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r) 
   if (!bk.bins) bk = plan_buckets(h, N, p->wf_priority != nullptr, sh.wave_path != 0);
   if (h->bucket_skip > 0) --h->bucket_skip;
   if (h->bin_skip > 0) --h->bin_skip;
-  if (h->rec_skip > 0) --h->rec_skip;
   rc = ensure_capacity(h, N, W, bk.nb, records_of(bk));
   if (rc != NALAR_OK) return rc;
   if (!sh.wave_path && !(h->flags & NALAR_FORCE_LEVEL_SWEEP)) {

@@ -51,6 +51,7 @@ struct Ctrl {
   uint32_t level_mask;           // priority levels seen (the next pass's bucket hint)
   uint32_t sort_level_pass;      // the last digit pass orders by priority level
   uint32_t unordered;            // the record sweep cannot take this snapshot (bucket_overflow is set too)
+  uint32_t higher;               // the order probe found a dependency at a higher id
   int64_t n_ready;
   int64_t slack_min;             // key range of the ready futures (all keys lie inside)
   int64_t slack_max;
@@ -170,6 +171,7 @@ struct HostStatus {
   uint32_t max_bucket; // futures in the fullest bucket (large-bucket sort only, else 0)
   uint32_t split_nb;   // bins the splitters written by this pass are for (0: none)
   uint32_t unordered;  // Ctrl::unordered (bin sort only)
+  uint32_t higher;     // Ctrl::higher (order probe only)
   uint32_t inc_rounds; // deepest rounds of an incremental pass that had work: closure | sweep << 8
 };
 
@@ -182,6 +184,7 @@ __device__ inline void reset_ctrl(Ctrl* c) {
     c->sort_npass = 0;
     c->sort_level_pass = 0;
     c->unordered = 0;
+    c->higher = 0;
     c->bucket_overflow = 0;
     c->n_ready = 0;
     c->slack_min = INT64_MAX;
@@ -209,6 +212,7 @@ __device__ inline void reset_ctrl_spread(Ctrl* c, int64_t gi, int64_t gstride) {
     c->sort_npass = 0;
     c->sort_level_pass = 0;
     c->unordered = 0;
+    c->higher = 0;
     c->bucket_overflow = 0;
     c->n_ready = 0;
     c->slack_min = INT64_MAX;

@@ -19,8 +19,11 @@
 // caller's order while it keys, routes and bins the ready futures.
 //
 // A snapshot with a dependency that does not lie lower sets Ctrl::unordered: the
-// pass is then done again by the block sweep, and the host leaves this path alone
-// for a while.
+// pass is then done again by the block sweep.  Done twice, that pass costs up to
+// 1.5 times one by the block sweep alone (348 us, so 525, for 1.3M futures of
+// 1,000 workflows; 1,360 and 1,860 for 4.6M of 256), so k_order_probe looks for
+// such a dependency first, behind a block sweep, and this path is taken only
+// behind a probe that found none.
 //
 // Per future k_rec moves about 45 bytes (6.6M: 84 us, 3.5 TB/s, with one line
 // written per run of records) and k_sweep_rec 24 (83 us: 26 chunks of about 3 us,
@@ -147,6 +150,34 @@ __global__ __launch_bounds__(kRecThreads) void k_rec(RecArgs a) {
   if (up) s_up = 1;
   __syncthreads();
   if (tid == 0 && s_up) flag_unordered(a.ctrl);
+}
+
+// Ids ascend with the position inside a workflow, so a dependency lies higher
+// exactly if its id does.  Of a longer list only the first kRecLight entries are
+// looked at: a miss costs the host one pass done twice.
+__global__ __launch_bounds__(kRecThreads) void k_order_probe(ProblemDev p, Ctrl* ctrl, HostStatus* host) {
+  if (ctrl->status) return;
+  const int64_t t0 = int64_t(blockIdx.x) * kRecTile + threadIdx.x;
+  int32_t o0[kRecPer], o1[kRecPer], d0[kRecPer];
+#pragma unroll
+  for (int j = 0; j < kRecPer; ++j) {
+    const int64_t v = t0 + j * kRecThreads;
+    o0[j] = v < p.N ? p.dep_off[v] : 0;
+    o1[j] = v < p.N ? p.dep_off[v + 1] : 0;
+  }
+#pragma unroll
+  for (int j = 0; j < kRecPer; ++j) d0[j] = o1[j] > o0[j] ? p.dep_idx[o0[j]] : -1;
+  bool up = false;
+#pragma unroll
+  for (int j = 0; j < kRecPer; ++j) {
+    const int64_t v = t0 + j * kRecThreads;
+    up |= d0[j] > v;
+    const int32_t e1 = o1[j] - o0[j] < kRecLight ? o1[j] : o0[j] + kRecLight;
+    for (int32_t e = o0[j] + 1; e < e1; ++e) up |= p.dep_idx[e] > v;
+  }
+  if (ballot(up) == 0 || lane_id() != 0 || ld_relaxed_agent(&ctrl->higher) != 0) return;
+  if (__hip_atomic_exchange(&ctrl->higher, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)  // the first wave tells
+    __hip_atomic_store(&host->higher, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ------------------------------------------------------------------- sweep
@@ -387,6 +418,11 @@ size_t sweep_rec_lds(int win) { return 8 * size_t(kRecT) * size_t(win); }
 hipError_t prepare_rec_kernels() {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep_rec), hipFuncAttributeMaxDynamicSharedMemorySize,
                              int(sweep_rec_lds(kRecWinOne)));
+}
+
+hipError_t launch_order_probe(hipStream_t s, const ProblemDev& p, Ctrl* ctrl, HostStatus* host) {
+  hipLaunchKernelGGL(k_order_probe, dim3(unsigned((p.N + kRecTile - 1) / kRecTile)), dim3(kRecThreads), 0, s, p, ctrl, host);
+  return hipGetLastError();
 }
 
 hipError_t launch_rec(hipStream_t s, const RecArgs& a) {

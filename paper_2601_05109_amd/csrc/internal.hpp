@@ -361,6 +361,8 @@ struct RecArgs {
 };
 hipError_t prepare_rec_kernels();  // LDS limit (at handle creation)
 hipError_t launch_rec(hipStream_t s, const RecArgs& a);
+// Whether a dependency lies at a higher id than its consumer (HostStatus::higher).
+hipError_t launch_order_probe(hipStream_t s, const ProblemDev& p, Ctrl* ctrl, HostStatus* host);
 hipError_t launch_sweep_rec(hipStream_t s, const RecArgs& a, int cus);
 
 // ingest.hip

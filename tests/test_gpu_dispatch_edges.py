@@ -435,3 +435,29 @@ def test_store_greedy_without_instances_after_a_load_overflow():
         g, inc = store_pass(pol, st, p, policy=G)
         assert inc, st.last_fallback
         assert_parity(g, oracle.run(p, policy=G), "without instances")
+
+
+@pytest.mark.parametrize("first", ["ordered", "unordered"])
+def test_record_sweep_is_left_alone_on_unordered_ids(first):
+    """A stream of snapshots whose ids are not in topological order never takes the
+    record sweep (which would do each pass twice), one that comes into order takes
+    it again within the passes between two looks, and one pass done twice is what a
+    stream that falls out of order costs."""
+    p, grouped = _grown_workflows(np.full(150, 900), 3)
+    mixed = wl.relabel(grouped, np.random.default_rng(3).permutation(p.n_nodes))
+    with nalar.Policy() as pol:
+        pol.set_timing(True)
+
+        def took_records(snapshot, passes):
+            taken = []
+            for rep in range(passes):
+                check(pol, snapshot, f"{snapshot is p} {rep}")
+                taken.append("records" in [k for k, _ in pol.timing()])
+            return taken
+
+        if first == "ordered":
+            assert took_records(p, 4) == [False, True, True, True]
+            assert sum(took_records(mixed, 12)) == 1
+        else:
+            assert not any(took_records(mixed, 12))
+        assert any(took_records(p, 18))
