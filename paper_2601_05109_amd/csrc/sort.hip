@@ -1065,9 +1065,9 @@ __global__ __launch_bounds__(T) void k_bin_sort(SortArgs a, BucketArgs bk) {
     }
   }
   Ctrl* ctrl = a.ctrl;
-  // (what the sweep by records found counts for nothing when it could not take
-  // the snapshot: the pass is done again)
-  const uint32_t status = ctrl->status | (ctrl->unordered ? 0u : ctrl->status_sweep);
+  // (what the sweep by records, whose bins have ties, found counts for nothing
+  // when it could not take the snapshot: the pass is done again)
+  const uint32_t status = ctrl->status | (kTie && ctrl->unordered ? 0u : ctrl->status_sweep);
   const uint32_t overflow = ctrl->bucket_overflow;
   RangeLanes rl;
   if (b == 0) rl = load_range_lanes(ctrl, a.levels != 0);
