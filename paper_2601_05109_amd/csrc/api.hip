@@ -1101,12 +1101,16 @@ int nalar::policy_pass_incremental(nalar_policy* h, const nalar_problem* p, nala
   ia.bk_clear_n = A.capB > 0 ? A.capB : 0;
   ia.stg_oslack = A.stg_oslack;
   ia.host = h->host;
-  // rounds with a launch of their own: as deep as the last pass had work (work
+  // Rounds with a launch of their own: as deep as the last pass had work (work
   // that comes deeper is done by the tail's one workgroup, and raises the next
-  // plan); an empty round costs a launch, 4 us.  A large delta gets them all: a
-  // few hundred thousand seeds leave thousands of futures to the rounds after the
-  // first, which one workgroup takes far longer over than the launches cost (325K
-  // seeds over 12.4M futures: 1,166 us, so 787).
+  // plan); an empty round costs a launch, 4 us.  A large delta gets the three
+  // that can have one, whatever the last pass was: behind an idle pass or a small
+  // one the rounds after the first hold thousands of futures, which the one
+  // workgroup takes longer over than the launches cost.  Three launches against
+  // the last pass's depth, behind an idle pass, in us: at 4,000 seeds 169 and 162
+  // (1.3M futures of 256 workflows), 373 and 387 (6.7M), 214 and 213 (0.77M of
+  // 2,000); at 8,000 172 and 163, 384 and 406, 223 and 234; at 16,000 282 and 314,
+  // 404 and 440, 239 and 271; at 32,000 291 and 327, 433 and 520, 242 and 317.
   const bool many = st.n_log + (N - st.n_prev) > kIncManySeeds;
   const int close_rounds = many ? kIncRounds : 1 + int(st.rounds & 0xFFu);
   const int sweep_rounds = many ? kIncRounds : 1 + int(st.rounds >> 8);

@@ -228,7 +228,7 @@ hipError_t launch_decide(hipStream_t s, const DecideArgs& a);
 // closure and of its sweep append to per-round lists (items of round r follow
 // those of rounds 0 .. r-1); the host launches kIncRounds rounds of each.
 constexpr int kIncRounds = 8;
-constexpr int64_t kIncManySeeds = 32768;  // seeds (completed and appended futures) of a delta that gets every round's launch
+constexpr int64_t kIncManySeeds = 8192;  // more seeds (completed and appended futures): see policy_pass_incremental
 constexpr uint32_t kIncRoundsAll = uint32_t(kIncRounds) | (uint32_t(kIncRounds) << 8);  // HostStatus::inc_rounds unknown
 constexpr int kIncHeavy = 64;     // more dependencies: one workgroup expands the future
 

@@ -461,3 +461,35 @@ def test_record_sweep_is_left_alone_on_unordered_ids(first):
         else:
             assert not any(took_records(mixed, 12))
         assert any(took_records(p, 18))
+
+
+@pytest.mark.parametrize("seeds", [8_000, 10_000, 40_000])
+def test_store_delta_behind_idle_passes(seeds):
+    """A delta of many futures behind passes without any: above 8,192 seeds the
+    rounds after the first get launches of their own, whatever the passes before
+    had to do (one workgroup takes them otherwise).  Chains of two and fan-ins make
+    several rounds."""
+    rng = np.random.default_rng(seeds)
+    W, n = 40, 3000
+    p = _rooted(W, n, lambda w, r: [(n - 1, range(1, n - 1, 29))], seeds)
+    with nalar.Policy() as pol, nalar.Store(pol) as st:
+        pol.set_timing(True)
+        prev = feed(st, p, 0, None)
+        store_pass(pol, st, p)
+        for tick in range(3):
+            for idle in range(2):
+                g, inc = store_pass(pol, st, p)
+                assert inc and st.last_fallback == 0
+            assert "inc_close_r1" not in [k for k, _ in pol.timing()]
+            open_ids = np.flatnonzero(p.done == 0)
+            ids = rng.choice(open_ids, seeds // 4, replace=False)
+            # children of children: the second half of the new futures hang on the first
+            first = rng.integers(0, p.n_nodes, (seeds - seeds // 4) // 2)
+            q = _extended(p, ids, first, tick)
+            q = _extended(q, [], p.n_nodes + np.arange(first.size), tick + 10)
+            prev = feed(st, q, *prev)
+            g, inc = store_pass(pol, st, q)
+            assert inc, st.last_fallback
+            assert_parity(g, oracle.run(q), f"{seeds} seeds, tick {tick}")
+            assert ("inc_close_r2" in [k for k, _ in pol.timing()]) == (seeds > 8192)
+            p = q
