@@ -116,28 +116,29 @@ def _extended(p, done_ids, parents, seed):
                       wf_contiguous=False)
 
 
+@pytest.mark.parametrize("order", [0, nalar.NALAR_ORDER_LPT, nalar.NALAR_ORDER_SRTF])
 @pytest.mark.parametrize("W", [3, 65_536, 65_537])
 @pytest.mark.parametrize("n", [1, 31, 32, 33, 65, 66, 255, 257, 2049, 4097, 70_001])
-def test_store_incremental_sizes(n, W):
+def test_store_incremental_sizes(n, W, order):
     """Incremental passes around the sizes their kernels work in (words of 32 and
     64 futures, units of 256, steps of 2,048 and 4,096), and around 65,536
-    workflows, up to which the records carry the workflow of a tie."""
+    workflows, up to which the records carry the workflow of a tie; under each order,
+    with splitters cut for it."""
     p = _fan_in_store(n, W, n + W)
     with nalar.Policy() as pol, nalar.Store(pol) as st:
         prev = feed(st, p, 0, None)
-        g, _ = store_pass(pol, st, p)
-        assert_parity(g, oracle.run(p), "full")
+        g, _ = store_pass(pol, st, p, policy=order)
+        assert_parity(g, oracle.run(p, policy=order), "full")
         rng = np.random.default_rng(n)
         for tick in range(3):
             every = np.arange(min(n, 300) - 1, dtype=np.int64)
             ids = every[tick::2] if tick < 2 else rng.choice(p.n_nodes, min(p.n_nodes, 40), replace=False)
             p = _extended(p, ids, rng.integers(0, p.n_nodes, 1 + tick * 40), tick)
             prev = feed(st, p, *prev)
-            g, inc = store_pass(pol, st, p, policy=(0, nalar.NALAR_ORDER_LPT, nalar.NALAR_ORDER_SRTF)[tick])
-            assert_parity(g, oracle.run(p, policy=(0, nalar.NALAR_ORDER_LPT, nalar.NALAR_ORDER_SRTF)[tick]),
-                          f"n={n} W={W} tick {tick}")
-            say(f"n={n} W={W} tick {tick}: incremental {inc}, reason {st.last_fallback}")
-            assert inc or tick > 0  # (another order's keys may overflow bins cut for this one)
+            g, inc = store_pass(pol, st, p, policy=order)
+            assert_parity(g, oracle.run(p, policy=order), f"n={n} W={W} order={order} tick {tick}")
+            say(f"n={n} W={W} order={order} tick {tick}: incremental {inc}, reason {st.last_fallback}")
+            assert inc
 
 
 # ---------------------------------------------------------------- wave sweep
@@ -240,7 +241,8 @@ def test_bin_sort_equal_keys(equal):
             q = _extended(q, rng.choice(q.n_nodes, 50, replace=False), rng.integers(0, q.n_nodes, 60), tick)
             prev = feed(st, q, *prev)
             g, inc = store_pass(pol, st, q)
-            assert_parity(g, oracle.run(q), f"{equal} equal keys, store tick {tick}, incremental {inc}")
+            assert inc, st.last_fallback
+            assert_parity(g, oracle.run(q), f"{equal} equal keys, store tick {tick}")
 
 
 # ---------------------------------------------------------------- record sweep
@@ -293,9 +295,10 @@ def _grown_workflows(sizes, seed):
 def test_record_sweep(W, n):
     """Workflows around whole chunks of 1,024 positions and around the chunks kept
     in LDS (19, or 9 for more workflows than the chip holds at once; the last size:
-    two such workflows among 298 small ones), ids by creation: the first pass sorts in tiles, the next ones take the record sweep; under other
-    policies; with one estimate too large to add up; and with ids that are not in
-    topological order, which go back to the block sweep."""
+    two such workflows among 298 small ones), ids by creation: the first pass sorts in
+    tiles, the next ones take the record sweep; under other policies; with a
+    dependency on another workflow; and with ids that are not in topological order,
+    which go back to the block sweep."""
     sizes = np.full(W, n)
     if W > 256:
         sizes[1:3] = 10_500
@@ -307,7 +310,9 @@ def test_record_sweep(W, n):
             assert rep not in (1, 2) or "records" in [k for k, _ in pol.timing()]
         pol.set_timing(False)
         q = p.copy()
-        q.dep_idx[np.flatnonzero(np.diff(q.dep_off) == 1)[5]] = 0 if q.wf[0] != q.wf[-1] else 1
+        v = np.flatnonzero((np.diff(q.dep_off) == 1) & (q.wf != q.wf[0]))[5]
+        q.dep_idx[q.dep_off[v]] = 0                         # a lower id, of another workflow
+        assert oracle.run(q).status == oracle.EINVAL
         check(pol, q, f"records W={W} n={n} foreign dependency")
         check(pol, p, f"records W={W} n={n} after it")
         rng = np.random.default_rng(n)
