@@ -141,7 +141,7 @@ struct nalar_policy {
   bool bucket_relaxed = false;   // the last pass tried fewer buckets
   int split_nb = 0;              // bins the current splitters are for (0: none)
   int split_cur = 0;             // the splitter buffer the next pass reads
-  bool rec_ok = false;           // the record sweep may be taken: the last look at the ids' order found none wrong
+  enum { kOrderUnknown, kOrderTopological, kOrderMixed } rec_order = kOrderUnknown;  // ids of the last large snapshot
   int rec_skip = 0;              // passes left before the order is looked at again
   int rec_backoff = 1;
   int bin_skip = 0;              // passes left before bins are tried again
@@ -738,20 +738,20 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
 
   // The record sweep (grouped.hip): a snapshot the library groups itself, of
   // workflows beyond the wave sweep, with bins planned; not where a testing flag
-  // asks for one of the block sweep's forms, and only behind a pass whose probe
-  // found the ids in topological order.  The probe runs behind the block sweep,
-  // on a handle's first large pass and, while it finds them in another order, 1, 2, 4 ...
-  // 64 passes apart (20 us at 1.3M futures, 50 at 4.6M).
+  // asks for one of the block sweep's forms, and not behind a snapshot whose ids
+  // were not in topological order.  A probe looks for that behind the block sweep:
+  // on a handle's first large pass if that has no bins yet, and after a snapshot out
+  // of order 1, 2, 4 ... 64 passes apart (20 us at 1.3M futures, 50 at 4.6M).
   const bool rec_able = N > 0 && node_of_pos && !sh.wave_path && own_splitters && !p->wf_priority &&
                         !(h->flags & (NALAR_FORCE_GLOBAL_SWEEP | NALAR_FORCE_LEVEL_SWEEP | NALAR_FORCE_TILED_SORT));
-  const bool rec = rec_able && bk.bins && h->rec_ok;
-  bool probe = rec_able && !h->rec_ok && (bk.bins || N >= kBinMinReady);
+  const bool rec = rec_able && bk.bins && h->rec_order != nalar_policy::kOrderMixed;
+  bool probe = rec_able && !rec && h->rec_order != nalar_policy::kOrderTopological && (bk.bins || N >= kBinMinReady);
   if (probe && h->rec_skip > 0) {
     --h->rec_skip;
     probe = false;
   }
   auto rec_back_off = [h]() {
-    h->rec_ok = false;
+    h->rec_order = nalar_policy::kOrderMixed;
     h->rec_skip = h->rec_backoff;
     h->rec_backoff = h->rec_backoff < 64 ? 2 * h->rec_backoff : 64;
   };
@@ -915,7 +915,10 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
       NALAR_LAUNCH("sweep", launch_sweep(s, sw, ba, sh));
     } else if (bk.bins) {
       h->bin_backoff = 1;
-      if (rec) h->rec_backoff = 1;
+      if (rec) {
+        h->rec_order = nalar_policy::kOrderTopological;
+        h->rec_backoff = 1;
+      }
       h->bin_max = __atomic_load_n(&h->host->max_bucket, __ATOMIC_ACQUIRE);
     } else {
       h->bucket_backoff = 1;
@@ -967,7 +970,7 @@ int run_pass(nalar_policy* h, const nalar_problem* p, nalar_result* r, ArenaStat
   r->n_ready = __atomic_load_n(&h->host->n_ready, __ATOMIC_ACQUIRE);
   if (probe) {
     if (__atomic_load_n(&h->host->higher, __ATOMIC_ACQUIRE) != 0) rec_back_off();
-    else h->rec_ok = true;
+    else h->rec_order = nalar_policy::kOrderTopological;
   }
   if (want_split || bk.bins) {  // splitters written for the next pass: read them from now on
     const uint32_t snb = __atomic_load_n(&h->host->split_nb, __ATOMIC_ACQUIRE);

@@ -498,3 +498,16 @@ def test_store_delta_behind_idle_passes(seeds):
             assert_parity(g, oracle.run(q), f"{seeds} seeds, tick {tick}")
             assert ("inc_close_r2" in [k for k, _ in pol.timing()]) == (seeds > 8192)
             p = q
+
+
+def test_record_sweep_on_a_handle_with_bins():
+    """A handle whose passes so far needed no grouping (nothing was looked at) takes
+    the record sweep at its first snapshot with ids by creation."""
+    p, grouped = _grown_workflows(np.full(150, 900), 4)
+    with nalar.Policy() as pol:
+        pol.set_timing(True)
+        for rep in range(2):
+            check(pol, grouped, f"grouped ids {rep}")
+        for rep in range(2):
+            check(pol, p, f"ids by creation {rep}")
+            assert "records" in [k for k, _ in pol.timing()]
