@@ -22,8 +22,8 @@
 // pass is then done again by the block sweep.  Done twice, that pass costs up to
 // 1.5 times one by the block sweep alone (348 us, so 525, for 1.3M futures of
 // 1,000 workflows; 1,360 and 1,860 for 4.6M of 256), so k_order_probe looks for
-// such a dependency first, behind a block sweep, and this path is taken only
-// behind a probe that found none.
+// such a dependency behind the block sweeps: on a handle's first pass, which has no
+// bins for this path yet, and after a snapshot out of order.
 //
 // Per future k_rec moves about 45 bytes (6.6M: 84 us, 3.5 TB/s, with one line
 // written per run of records) and k_sweep_rec 24 (83 us: 26 chunks of about 3 us,
@@ -184,7 +184,10 @@ __global__ __launch_bounds__(kRecThreads) void k_order_probe(ProblemDev p, Ctrl*
 
 constexpr int kRecT = 1024;           // positions per chunk, one per thread
 // Chunks whose maxima are in LDS: as many as fit when the chip holds every
-// workflow at once with one workgroup per CU, else as many as fit twice.
+// workflow at once with one workgroup per CU, else as many as fit twice.  19 and 9
+// chunks, in us of this kernel: 24 workflows of 23K futures 63 and 70, 100 of 23K
+// 65 and 75, 64 of 20K 69 and 75, 128 of 10K 43 and 43; 500 of 2.5K 32 and 31,
+// 1,000 of 5K 92 and 89, 4,000 of 1.3K 160 and 152, but 300 of 14K 86 and 92.
 constexpr int kRecWinOne = 19, kRecWinTwo = 9;
 
 __device__ inline void lds_max(int64_t* p, int64_t v) {

@@ -29,9 +29,10 @@
 // all but one to its workgroup's LDS queue, and a future with more than
 // kIncHeavy dependencies goes to a second LDS queue whose futures the whole
 // workgroup expands together; the workgroup drains both before it ends.  A
-// full queue spills into the next round's lists; the host launches kIncRounds
-// rounds, and work left after the last one makes the pass fall back to a
-// full pass (kStIncomplete).
+// full queue spills into the next round's lists.  Of the kIncRounds rounds the
+// first one to three get a launch each and one workgroup runs the others in one
+// launch; work left after the last round makes the pass fall back to a full
+// pass (kStIncomplete).
 #include "internal.hpp"
 
 namespace nalar {
@@ -1087,11 +1088,8 @@ hipError_t launch_inc_clear(hipStream_t s, uint32_t* p, int64_t n) {
   return hipGetLastError();
 }
 
-constexpr const char* kCloseNames[kIncRounds] = {"inc_close_r0", "inc_close_r1", "inc_close_r2", "inc_close_r3",
-                                                  "inc_close_r4", "inc_close_r5", "inc_close_r6", "inc_close_r7"};
-constexpr const char* kSweepNames[kIncRounds] = {"inc_sweep_r0", "inc_sweep_r1", "inc_sweep_r2", "inc_sweep_r3",
-                                                  "inc_sweep_r4", "inc_sweep_r5", "inc_sweep_r6", "inc_sweep_r7"};
-static_assert(kIncRounds == 8, "one name per round");
+constexpr const char* kCloseNames[kIncTail] = {"inc_close_r0", "inc_close_r1", "inc_close_r2"};
+constexpr const char* kSweepNames[kIncTail] = {"inc_sweep_r0", "inc_sweep_r1", "inc_sweep_r2"};
 
 hipError_t launch_inc_closure(hipStream_t s, const IncArgs& a, int cus, int rounds,
                               void (*mark)(void*, const char*), void* ctx) {

@@ -226,7 +226,8 @@ hipError_t launch_decide(hipStream_t s, const DecideArgs& a);
 
 // Incremental pass over the graph store (incremental.hip).  Rounds of the
 // closure and of its sweep append to per-round lists (items of round r follow
-// those of rounds 0 .. r-1); the host launches kIncRounds rounds of each.
+// those of rounds 0 .. r-1); there are kIncRounds rounds of each, the first one
+// to three with a launch of their own, the others in one workgroup's launch.
 constexpr int kIncRounds = 8;
 constexpr int64_t kIncManySeeds = 8192;  // more seeds (completed and appended futures): see policy_pass_incremental
 constexpr uint32_t kIncRoundsAll = uint32_t(kIncRounds) | (uint32_t(kIncRounds) << 8);  // HostStatus::inc_rounds unknown

@@ -47,7 +47,9 @@ constexpr int kWTile = kWThreads * kWItems;   // positions per workgroup tile
 // Up to this many tiles of the whole id space the assign kernel sums the
 // earlier tiles' counts itself: one load per slot and tile, in flight together,
 // against a launch of its own for the scan (about 4 us); beyond, the sum's
-// length would show.
+// length would show.  The line is drawn by the id space, since the host launches
+// these kernels before the ready count is known: a large snapshot with few ready
+// futures pays for the scan launch as well.
 constexpr int64_t kWDirectTiles = 256;
 constexpr int kWTableThreads = 1024;
 constexpr int kSlotBits = 10;             // slots < NALAR_MAX_INSTANCES = 2^10
