@@ -1224,9 +1224,18 @@ constexpr int64_t kGroupWTiles = 2048;                              // tiles bef
 // workflows, whose columns are long
 constexpr int kGroupWScan = 1024, kGroupWCols = 64, kGroupWFewCols = 4, kGroupWPer = 8;
 
+// Above this many workflows a tile is 8,192 ids, and its workgroup's walk through
+// them (41 us and more in the placing kernel) is not spread over the chip by few
+// ids: workflows of fewer than 24 on average keep the radix passes.  Whole passes,
+// radix and this grouping, in us: 8,193 workflows of 4 / 16 / 32 ids 87 / 105 / 124
+// and 94 / 107 / 119; 16,384 of them 106 / 136 / 172 and 115 / 134 / 160; but 8,192
+// (tiles of 4,096) of 4 84 and 73.
+constexpr int64_t kGroupWWide = 8192, kGroupWWideIds = 24;
+
 // Ids per tile, or 0 when this grouping does not apply.
 int64_t groupw_tile(int64_t N, int64_t W, int64_t cap_n) {
   if (W > kGroupWMax || W > cap_n) return 0;
+  if (W > kGroupWWide && N < kGroupWWideIds * W) return 0;
   int64_t tile = kGroupWSub;
   while (tile * 2 < W || (N > tile * kGroupWTiles && tile < kGroupWMax)) tile *= 2;
   const int64_t tiles = (N + tile - 1) / tile;

@@ -213,6 +213,24 @@ def test_grouping_by_many_workflows(policy, W, n):  # noqa: F811
         check(policy, r, f"grouped W={W} n={n} pass {rep}", flags=0)
 
 
+@pytest.mark.parametrize("W,n,counted", [(8192, 3, True), (8193, 3, False), (8193, 23, False), (8193, 24, True),
+                                         (16_384, 23, False), (16_384, 24, True), (16_385, 24, False)])
+def test_grouping_of_small_workflows(policy, W, n, counted):  # noqa: F811
+    """Many small workflows with ids in random order: the radix passes group what
+    the counting kernels' tiles of 8,192 ids would leave to a few workgroups."""
+    p = _independent(W * n, 24, 5, W + n)
+    rng = np.random.default_rng(n)
+    p = p.copy(wf=rng.permutation(np.repeat(np.arange(W, dtype=np.int32), n)),
+               deadline_us=(p.now_us + rng.integers(0, 10**7, W)).astype(np.int64), wf_contiguous=False)
+    policy.set_timing(True)
+    try:
+        for rep in range(2):
+            check(policy, p, f"{W} workflows of {n} pass {rep}")
+            assert ("group_count" in [k for k, _ in policy.timing()]) == counted
+    finally:
+        policy.set_timing(False)
+
+
 # ---------------------------------------------------------------- bin sort
 
 @pytest.mark.parametrize("equal", [1, 31, 33, 127, 128, 129, 300])
