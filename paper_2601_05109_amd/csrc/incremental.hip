@@ -466,8 +466,8 @@ __device__ void scan_heavy(const IncArgs& a, uint32_t first, uint32_t step) {
 // word.  The ready futures leave as one bit each, written per wave (a list
 // cost one returning atomic per workgroup on its length, all queued on that
 // word), and the member count goes to spread words.  At 12.4M futures 191 us,
-// and 17 us for the futures of many dependencies, became 73 us together; at
-// 1.3M 39 + 13 became 19.
+// and 17 us for the futures of many dependencies, became 70 us together; at
+// 1.3M 39 + 13 became 21.
 __global__ __launch_bounds__(kIncThreads) void k_inc_scan(IncArgs a, int hb) {
   if (invalid(a)) return;
   if (int(blockIdx.x) < hb) {
@@ -806,9 +806,9 @@ __device__ inline int64_t key_of(uint32_t policy, int64_t rem, int64_t dl) {
 // memory side, about 12 per ns on the whole chip) and the sparse gathers bound
 // it, so a workgroup is as large as it can be, and a chunk as long: half the
 // segments of 1,024-future chunks over 256-thread workgroups.  At 12.4M futures,
-// 2.3M ready, 159 us and a 40 us copy of rem became 155 us, and 134 us with the
+// 2.3M ready, 159 us and a 40 us copy of rem became 155 us, and 142 us with the
 // attributes gathered as one record per future instead of four arrays; at 1.3M
-// 42 + 5 became 34 (512 threads, in chunks of 4,096 or 8,192: 42 to 47).
+// 42 + 5 became 40 (512 threads, in chunks of 4,096 or 8,192: 42 to 47).
 constexpr int kReadyThreads = 1024;
 constexpr int kReadyPer = 8;                          // ready futures per thread and chunk
 constexpr int kReadyChunk = kReadyPer * kReadyThreads;
